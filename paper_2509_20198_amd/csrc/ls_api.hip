@@ -71,7 +71,8 @@ int ls_conv_num_configs_impl(int layer, int precision, int pass) {
   //   activations are not kept (the head's default)
   // BF16 input gradient: 0 / 1 = direct with 4 / 2 pixel tiles per wave,
   //   2 = persistent LDS tile (the default)
-  // FP32 conv (forward, input gradient): 0..3 = channel block cap 32, 16, 8, 4
+  // FP32 conv (forward, input gradient): 0 = tiles by size (the default),
+  //   1 = 8 x 4 pixels per wave, 2 = 8 x 8, 3 = 8 x 4 and twice the waves
   // weight gradient (both precisions): 0..2 = 512, 256, 128 pixel chunks;
   //   BF16 also 3..5 = the same on the matrix cores (im2col slabs) and
   //   6..8 = the same on the matrix cores by 16 x 16 output tiles

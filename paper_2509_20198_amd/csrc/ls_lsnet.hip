@@ -23,14 +23,14 @@
 // (block-diagonal weights: each encoder's 16 outputs see only its own input
 // channels, the other weights are exact zeros), the later layers as one
 // launch per encoder reading its 16 or 32 channels out of the shared tensor
-// and writing its slice of the next one; the BF16 path fuses every pool into
-// the conv epilogue, so only pooled encoder activations are stored.  The two
+// and writing its slice of the next one; every pool is fused into the conv
+// epilogue, so only pooled encoder activations are stored.  The two
 // FC1 layers are one GEMM over the interleaved encoder features (zero
 // blocks where an FC1 layer does not read an encoder), and the two FC2
 // layers one GEMM whose output columns are permuted so that it is directly
 // the decoders' shared 64-channel input image.  Convolutions use the
-// library's conv kernels (FP32 vector, or BF16 on the matrix cores with FP32
-// accumulation); the fully connected layers have their own kernels
+// library's conv kernels (FP32, or BF16 with FP32 accumulation, both on the
+// matrix cores); the fully connected layers have their own kernels
 // (tiled FP32, or BF16 on v_mfma_f32_16x16x32_bf16).  The batch is taken in
 // chunks so the workspace stays bounded.
 #include <algorithm>
@@ -94,8 +94,8 @@ Net make_net(int R) {
 // Every derived weight array is one segment; a thread per destination
 // element finds its segment and computes the element.
 enum SegKind {
-  S_CONV_T = 0,   // FP32 [tap][cin][cout] from W[cout][tap][cin]
-  S_ENC1_T = 1,   // FP32 [tap][8][64], the four first encoder layers block-diagonally
+  S_CONV_T = 0,   // FP32 conv weights, packed (ls_conv_f32_element)
+  S_ENC1_T = 1,   // the four first encoder layers block-diagonally as one 8 -> 64 conv, packed
   S_ENC1_B = 2,   // FP32 [64] their biases
   S_FC1_T = 3,    // FP32 [4L][512] (K x N) of the joint FC1
   S_FC1_B = 4,    // FP32 [512]
@@ -177,12 +177,14 @@ __global__ void k_lsnet_prep(PrepArgs A) {
       const int cin = g.cin, cout = g.cout;
       switch (g.kind) {
         case S_CONV_T: {
-          const int tap = (int)(r / ((int64_t)cin * cout)), ci = (int)((r / cout) % cin), co = (int)(r % cout);
-          A.f32[g.dst + r] = conv_value(A, g.layer, cin, co, tap, ci);
+          int co, tap, ci;
+          ls_conv_f32_element(cin, r, co, tap, ci);
+          A.f32[g.dst + r] = co < cout ? conv_value(A, g.layer, cin, co, tap, ci) : 0.f;
           break;
         }
         case S_ENC1_T: {
-          const int tap = (int)(r / (8 * 64)), ci = (int)((r / 64) % 8), co = (int)(r % 64);
+          int co, tap, ci;
+          ls_conv_f32_element(8, r, co, tap, ci);
           A.f32[g.dst + r] = enc1_value(A, co, tap, ci);
           break;
         }
@@ -371,7 +373,7 @@ __global__ void k_lsnet_epilogue(const float* __restrict__ head, const float* __
 // ------------------------------------------------------------------ host side
 struct Derived {
   // FP32 path
-  int64_t conv_t[NL];  // per conv layer (except the first encoder layers), [9][cin][cout]
+  int64_t conv_t[NL];  // per conv layer (except the first encoder layers), packed
   int64_t enc1_t, enc1_b, fc1_t, fc1_b, fc2_t, fc2_b;
   int64_t n_f32;
   // BF16 path
@@ -409,8 +411,9 @@ Derived derive(const Net& n, int precision) {
       const bool first_enc = k < L_FC1H && k % 4 == 0;
       if (l.kind != CONV || first_enc) continue;
       d.conv_t[k] = f;
-      seg(S_CONV_T, k, l.cin, l.cout, 0, f, 9LL * l.cin * l.cout);
-      f += 9LL * l.cin * l.cout;
+      const int64_t np = ls_conv_f32_packed(l.cin, l.cout);
+      seg(S_CONV_T, k, l.cin, l.cout, 0, f, np);
+      f += np;
     }
     d.fc1_t = f;
     seg(S_FC1_T, 0, 0, 0, 0, f, 4 * L * 512);
@@ -446,13 +449,13 @@ Derived derive(const Net& n, int precision) {
 
 constexpr int CHUNK_F32 = 256, CHUNK_BF16 = 1024;
 
-// Activation elements per tile (FP32 path stores the full-resolution encoder
-// outputs before pooling; the BF16 path pools in the conv epilogue).
+// Activation elements per tile (the convs pool the encoder outputs in their
+// epilogues).
 struct Acts {
-  int64_t e1, p1, e2, p2, e3, p3, e4, feat, z, d, dd1, dd2, dd3, aht, f1, f2, head, total;
+  int64_t p1, p2, p3, feat, z, d, dd1, dd2, dd3, aht, f1, f2, head, total;
 };
 
-Acts acts_per_tile(int R, int res, bool full_enc) {
+Acts acts_per_tile(int R, int res) {
   Acts a{};
   const int64_t r2 = (int64_t)R * R;
   int64_t o = 0;
@@ -461,13 +464,9 @@ Acts acts_per_tile(int R, int res, bool full_enc) {
     o += (n + 63) / 64 * 64;
     return at;
   };
-  if (full_enc) a.e1 = take(r2 * 64);
   a.p1 = take(r2 / 4 * 64);
-  if (full_enc) a.e2 = take(r2 / 4 * 128);
   a.p2 = take(r2 / 16 * 128);
-  if (full_enc) a.e3 = take(r2 / 16 * 128);
   a.p3 = take(r2 / 64 * 128);
-  if (full_enc) a.e4 = take(r2 / 64 * 128);
   a.feat = take(r2 / 256 * 128);
   a.z = take(512);
   a.d = take(r2 / 256 * 64);
@@ -486,7 +485,7 @@ size_t ws_bytes(const LsGridInfo& gi, int32_t n_tiles, int precision) {
   const Net n = make_net(gi.R);
   const Derived d = derive(n, precision);
   const int chunk = std::max(1, std::min<int>(n_tiles, precision == LS_FP32 ? CHUNK_F32 : CHUNK_BF16));
-  const Acts a = acts_per_tile(gi.R, gi.res, precision == LS_FP32);
+  const Acts a = acts_per_tile(gi.R, gi.res);
   const size_t el = precision == LS_FP32 ? 4 : 2;
   return ls_align((size_t)d.n_f32 * 4) + ls_align((size_t)d.n_bf16 * 2) + ls_align((size_t)a.total * el * chunk) +
          ls_align((size_t)gi.res * gi.res * 4 * 4 * chunk) + 1024;
@@ -535,9 +534,10 @@ SrcPart part_bf16(const uint16_t* p, int c, int hw, int stride, int coff, bool u
   return s;
 }
 
-// FP32 conv over a whole H x H plane (or the crop window) into a channel slice.
+// FP32 conv over a whole H x H plane (or the crop window) into a channel
+// slice, of its 2 x 2 average pool only where `pool` is set.
 int conv32(const ConvSrc& s, int B, int H, const float* wt, const float* bias, int cout, int relu, float* out,
-           int out_stride, int out_coff, int y0, int x0, int Ho, hipStream_t st) {
+           int out_stride, int out_coff, int y0, int x0, int Ho, hipStream_t st, bool pool = false) {
   ConvArgs a;
   a.src = s;
   a.B = B;
@@ -551,10 +551,11 @@ int conv32(const ConvSrc& s, int B, int H, const float* wt, const float* bias, i
   a.bias = bias;
   a.cout = cout;
   a.relu = relu;
-  a.out = out;
-  a.out_stride = out_stride;
-  a.out_coff = out_coff;
-  a.cob_max = 32;
+  a.out = pool ? nullptr : out;
+  a.pool_out = pool ? out : nullptr;
+  a.out_stride = a.pool_stride = out_stride;
+  a.out_coff = a.pool_coff = out_coff;
+  a.tiling = 0;
   return ls_conv_f32(a, st);
 }
 
@@ -639,7 +640,7 @@ int ls_lsnet_forward_impl(const float* w, int precision, int inputs, const float
   const Derived d = derive(net, precision);
   const bool f32 = precision == LS_FP32;
   const int chunk = std::min<int>(n_tiles, f32 ? CHUNK_F32 : CHUNK_BF16);
-  const Acts at = acts_per_tile(R, res, f32);
+  const Acts at = acts_per_tile(R, res);
   LsArena ar{reinterpret_cast<char*>(ws), ws_bytes_given, 0};
   float* wf = ar.take<float>(d.n_f32);
   uint16_t* wb = ar.take<uint16_t>(d.n_bf16 > 0 ? d.n_bf16 : 1);
@@ -681,30 +682,25 @@ int ls_lsnet_forward_impl(const float* w, int precision, int inputs, const float
     if (f32) {
       float* A0 = act32;
       auto P = [&](int64_t off) { return A0 + off * B; };
-      float *E1 = P(at.e1), *P1 = P(at.p1), *E2 = P(at.e2), *P2 = P(at.p2), *E3 = P(at.e3), *P3 = P(at.p3),
-            *E4 = P(at.e4), *Fe = P(at.feat), *Z = P(at.z), *D = P(at.d), *Dd1 = P(at.dd1), *Dd2 = P(at.dd2),
-            *Dd3 = P(at.dd3), *Aht = P(at.aht), *F1 = P(at.f1), *F2 = P(at.f2);
-      // encoders
-      LS_TRYN(conv32(src1(X), B, R, wf + d.enc1_t, wf + d.enc1_b, 64, 1, E1, 64, 0, 0, 0, R, st));
-      LS_TRYN(ls_avgpool_f32(E1, P1, B, R, R, 64, st));
+      float *P1 = P(at.p1), *P2 = P(at.p2), *P3 = P(at.p3), *Fe = P(at.feat), *Z = P(at.z), *D = P(at.d),
+            *Dd1 = P(at.dd1), *Dd2 = P(at.dd2), *Dd3 = P(at.dd3), *Aht = P(at.aht), *F1 = P(at.f1), *F2 = P(at.f2);
+      // encoders: pooled outputs only
+      LS_TRYN(conv32(src1(X), B, R, wf + d.enc1_t, wf + d.enc1_b, 64, 1, P1, 64, 0, 0, 0, R, st, true));
       for (int e = 0; e < 4; ++e) {
         const int l = L_ENC + 4 * e + 1;
         LS_TRYN(conv32(src1(part_f32(P1, 16, R2, 64, 16 * e, false)), B, R2, wf + d.conv_t[l], w + net.boff[l], 32,
-                       1, E2, 128, 32 * e, 0, 0, R2, st));
+                       1, P2, 128, 32 * e, 0, 0, R2, st, true));
       }
-      LS_TRYN(ls_avgpool_f32(E2, P2, B, R2, R2, 128, st));
       for (int e = 0; e < 4; ++e) {
         const int l = L_ENC + 4 * e + 2;
         LS_TRYN(conv32(src1(part_f32(P2, 32, R4, 128, 32 * e, false)), B, R4, wf + d.conv_t[l], w + net.boff[l], 32,
-                       1, E3, 128, 32 * e, 0, 0, R4, st));
+                       1, P3, 128, 32 * e, 0, 0, R4, st, true));
       }
-      LS_TRYN(ls_avgpool_f32(E3, P3, B, R4, R4, 128, st));
       for (int e = 0; e < 4; ++e) {
         const int l = L_ENC + 4 * e + 3;
         LS_TRYN(conv32(src1(part_f32(P3, 32, R8, 128, 32 * e, false)), B, R8, wf + d.conv_t[l], w + net.boff[l], 32,
-                       1, E4, 128, 32 * e, 0, 0, R8, st));
+                       1, Fe, 128, 32 * e, 0, 0, R8, st, true));
       }
-      LS_TRYN(ls_avgpool_f32(E4, Fe, B, R8, R8, 128, st));
       // merge
       LS_TRYN(fc_f32(Fe, wf + d.fc1_t, wf + d.fc1_b, Z, B, 512, (int)(4 * L), st));
       LS_TRYN(fc_f32(Z, wf + d.fc2_t, wf + d.fc2_b, D, B, (int)(2 * L), 512, st));

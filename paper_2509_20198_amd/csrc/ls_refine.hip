@@ -35,8 +35,8 @@ Acts act_layout(int R) {
 enum { iA1, iA2, iP1, iA3, iA4, iP2, iA5, iA6, iA7, iA8, iA9, iA10 };
 
 struct RefineWs {
-  float* wt;
-  float* wd;
+  float* wt;       // packed FP32 weights of the forward
+  float* wd;       // and of the input gradients
   uint16_t* wbt;   // BF16 [tap][cin][cout] copies (BF16 path)
   void* acts;      // activations when the caller keeps none
   float* head;     // [B][res][res][4]
@@ -58,8 +58,8 @@ size_t refine_layout(const LsGridInfo& gi, int32_t B, int precision, int backwar
   const int64_t f = (int64_t)R * R, h = f / 4, q = f / 16;
   const Acts al = act_layout(R);
   const size_t esz = precision == LS_BF16 ? 2 : 4;
-  W->wt = A.take<float>(LS_NUM_PARAMS);
-  W->wd = A.take<float>(LS_NUM_PARAMS);
+  W->wt = A.take<float>(ls_f32_packed_offset(LS_NLAYER, false));
+  W->wd = A.take<float>(ls_f32_packed_offset(LS_NLAYER, true));
   W->wbt = A.take<uint16_t>(ls_bf16_packed_total());
   W->acts = need_acts ? (void*)A.take<char>((size_t)al.per_tile * B * esz) : nullptr;
   W->head = A.take<float>((int64_t)B * res * res * 4);
@@ -107,14 +107,23 @@ ConvArgs conv_args(const ConvSrc& s, int B, int H, const float* wt, const float*
   a.x0 = 0;
   a.Ho = H;
   a.Wo = H;
-  a.wt = wt + ls_layer_w_offset(l);
+  a.wt = wt + ls_f32_packed_offset(l, false);
   a.bias = w ? w + ls_layer_b_offset(l) : nullptr;
   a.cout = LS_LAYERS[l].cout;
   a.relu = relu;
   a.out = out;
   a.out_stride = a.cout;
   a.out_coff = 0;
-  a.cob_max = ls_cob_for_config(ls_conv_config_get(l, LS_FP32, 0));
+  a.pool_out = nullptr;
+  a.pool_stride = a.pool_coff = 0;
+  a.tiling = ls_f32_tiling_for_config(ls_conv_config_get(l, LS_FP32, 0));
+  return a;
+}
+
+// the same with the 2 x 2 average pool of the output
+ConvArgs with_pool(ConvArgs a, float* pool) {
+  a.pool_out = pool;
+  a.pool_stride = a.cout;
   return a;
 }
 
@@ -138,30 +147,41 @@ SrcPart up(SrcPart p) {
 }
 
 // FP32 forward through all layers; acts points at the FP32 activation block.
+// Without `keep` (nothing reads the activations afterwards) dec1a and dec1b
+// run only on the crop grown by the two and one texels the next layers read
+// (half of their products at the 96 x 96 grid), as window tensors.
 int forward_f32(const float* w, const float* wt, const float* x, int B, const LsGridInfo& gi, float* acts, float* head,
-                hipStream_t st) {
+                bool keep, hipStream_t st) {
   const int R = gi.R, R2 = R / 2, R4 = R / 4;
   const Acts al = act_layout(R);
   auto A = [&](int i) { return acts + al.off[i] * B; };
   auto P = [&](int i, int c, int hw) { return src_plain(A(i), c, hw, hw, c, 0, nullptr); };
   const SrcPart X = src_plain(x, 8, R, R, 8, 0, nullptr);
   LS_TRY(ls_conv_f32(conv_args(one(X), B, R, wt, w, E1A, A(iA1), 1), st));
-  LS_TRY(ls_conv_f32(conv_args(one(P(iA1, 16, R)), B, R, wt, w, E1B, A(iA2), 1), st));
-  LS_TRY(ls_avgpool_f32(A(iA2), A(iP1), B, R, R, 16, st));
+  LS_TRY(ls_conv_f32(with_pool(conv_args(one(P(iA1, 16, R)), B, R, wt, w, E1B, A(iA2), 1), A(iP1)), st));
   LS_TRY(ls_conv_f32(conv_args(one(P(iP1, 16, R2)), B, R2, wt, w, E2A, A(iA3), 1), st));
-  LS_TRY(ls_conv_f32(conv_args(one(P(iA3, 32, R2)), B, R2, wt, w, E2B, A(iA4), 1), st));
-  LS_TRY(ls_avgpool_f32(A(iA4), A(iP2), B, R2, R2, 32, st));
+  LS_TRY(ls_conv_f32(with_pool(conv_args(one(P(iA3, 32, R2)), B, R2, wt, w, E2B, A(iA4), 1), A(iP2)), st));
   LS_TRY(ls_conv_f32(conv_args(one(P(iP2, 32, R4)), B, R4, wt, w, BA, A(iA5), 1), st));
   LS_TRY(ls_conv_f32(conv_args(one(P(iA5, 64, R4)), B, R4, wt, w, BB, A(iA6), 1), st));
   LS_TRY(ls_conv_f32(conv_args(two(up(P(iA6, 64, R4)), P(iA4, 32, R2)), B, R2, wt, w, D2A, A(iA7), 1), st));
   LS_TRY(ls_conv_f32(conv_args(one(P(iA7, 32, R2)), B, R2, wt, w, D2B, A(iA8), 1), st));
-  LS_TRY(ls_conv_f32(conv_args(two(up(P(iA8, 32, R2)), P(iA2, 16, R)), B, R, wt, w, D1A, A(iA9), 1), st));
-  LS_TRY(ls_conv_f32(conv_args(one(P(iA9, 16, R)), B, R, wt, w, D1B, A(iA10), 1), st));
-  ConvArgs h = conv_args(two(P(iA10, 16, R), X), B, R, wt, w, HEAD, head, 0);
-  h.y0 = gi.pad;
-  h.x0 = gi.pad;
-  h.Ho = gi.res;
-  h.Wo = gi.res;
+  const Lvl1Win lw = ls_lvl1_windows(R, gi.pad, gi.res);
+  SrcPart a9 = P(iA9, 16, keep ? R : lw.dn), a10 = P(iA10, 16, keep ? R : lw.hn);
+  auto window = [](ConvArgs a, int y0, int n) {
+    a.y0 = a.x0 = y0;
+    a.Ho = a.Wo = n;
+    return a;
+  };
+  ConvArgs d1a = conv_args(two(up(P(iA8, 32, R2)), P(iA2, 16, R)), B, R, wt, w, D1A, A(iA9), 1);
+  if (!keep) {
+    a9.oy = a9.ox = lw.d0;
+    a10.oy = a10.ox = lw.h0;
+    d1a = window(d1a, lw.d0, lw.dn);
+  }
+  LS_TRY(ls_conv_f32(d1a, st));
+  ConvArgs d1b = conv_args(one(a9), B, R, wt, w, D1B, A(iA10), 1);
+  LS_TRY(ls_conv_f32(keep ? d1b : window(d1b, lw.h0, lw.hn), st));
+  const ConvArgs h = window(conv_args(two(a10, X), B, R, wt, w, HEAD, head, 0), gi.pad, gi.res);
   LS_TRY(ls_conv_f32(h, st));
   return LS_OK;
 }
@@ -249,14 +269,16 @@ int dgrad(const float* wd, int l, const float* dA, const float* mask, int B, int
   a.x0 = 0;
   a.Ho = H;
   a.Wo = H;
-  a.wt = wd + ls_layer_w_offset(l);
+  a.wt = wd + ls_f32_packed_offset(l, true);
   a.bias = nullptr;
   a.cout = cin;
   a.relu = 0;
   a.out = out;
   a.out_stride = cin;
   a.out_coff = 0;
-  a.cob_max = ls_cob_for_config(ls_conv_config_get(l, LS_FP32, 1));
+  a.pool_out = nullptr;
+  a.pool_stride = a.pool_coff = 0;
+  a.tiling = ls_f32_tiling_for_config(ls_conv_config_get(l, LS_FP32, 1));
   return ls_conv_f32(a, st);
 }
 
@@ -282,14 +304,16 @@ int backward_f32(const float* w, const float* wd, const float* x, const float* a
     a.x0 = 0;
     a.Ho = R;
     a.Wo = R;
-    a.wt = wd + ls_layer_w_offset(HEAD);
+    a.wt = wd + ls_f32_packed_offset(HEAD, true);
     a.bias = nullptr;
     a.cout = 24;
     a.relu = 0;
     a.out = W.dXC;
     a.out_stride = 24;
     a.out_coff = 0;
-    a.cob_max = ls_cob_for_config(ls_conv_config_get(HEAD, LS_FP32, 1));
+    a.pool_out = nullptr;
+    a.pool_stride = a.pool_coff = 0;
+    a.tiling = ls_f32_tiling_for_config(ls_conv_config_get(HEAD, LS_FP32, 1));
     LS_TRY(ls_conv_f32(a, st));
   }
   LS_TRY(wgrad(two(P(iA10, 16, R), X), B, R, HEAD, grad_y, nullptr, 4, pad, pad, res, res, grad_w, W.partial, st));
@@ -519,8 +543,8 @@ int ls_refine_forward_impl(const float* w, const uint16_t* w_bf16, int precision
   void* acts = act_save ? act_save : W.acts;
   const double r_m = (double)gi.H * gi.scale_xy;
   if (precision == LS_FP32) {
-    LS_TRY(ls_prep_weights(w, W.wt, W.wd, st));
-    LS_TRY(forward_f32(w, W.wt, x, n_tiles, gi, reinterpret_cast<float*>(acts), W.head, st));
+    LS_TRY(ls_prep_weights(w, W.wt, nullptr, st));
+    LS_TRY(forward_f32(w, W.wt, x, n_tiles, gi, reinterpret_cast<float*>(acts), W.head, act_save != nullptr, st));
   } else {
     LS_TRY(ls_bf16_prep_weights(w_bf16, W.wbt, st));
     LS_TRY(ls_bf16_forward(w, W.wbt, x, n_tiles, gi, reinterpret_cast<uint16_t*>(acts), W.head, act_save == nullptr,
@@ -541,7 +565,7 @@ int ls_refine_backward_impl(const float* w, const uint16_t* w_bf16, int precisio
     LS_TRY(ls_prep_weights(w, W.wt, W.wd, st));
     const float* acts = reinterpret_cast<const float*>(act_save);
     if (!acts) {
-      LS_TRY(forward_f32(w, W.wt, x, n_tiles, gi, reinterpret_cast<float*>(W.acts), W.head, st));
+      LS_TRY(forward_f32(w, W.wt, x, n_tiles, gi, reinterpret_cast<float*>(W.acts), W.head, true, st));
       acts = reinterpret_cast<const float*>(W.acts);
     }
     return backward_f32(w, W.wd, x, acts, grad_y, n_tiles, gi, grad_w, grad_x, W, st);

@@ -6,11 +6,10 @@
 // upsampling, channel concatenation of two tensors, embedding a smaller
 // tensor at an offset (the head's crop window, seen from the backward), and
 // the ReLU mask of the backward (a value counts only where the forward
-// activation was positive).  Average pooling writes its own small tensor.
+// activation was positive).
 //
-// FP32 path ("plain"): one launch per layer over the whole batch, each lane
-// one output pixel x COB output channels, weights read as wave-uniform
-// scalars from a [tap][cin][cout] copy.  BF16 path: see ls_unet_bf16.hip.
+// Here: weight preparation, weight gradients, and the elementwise passes.
+// The convolutions are in ls_conv_f32.hip (FP32) and ls_unet_bf16.hip (BF16).
 #include <algorithm>
 #include <vector>
 
@@ -21,121 +20,34 @@ namespace {
 
 constexpr int CT = 256;
 
+// One thread per packed element (ls_conv_f32_element) of every layer: the
+// forward's, then the input gradients' (the conv of the output gradient with
+// the turned weights, whose input channels are the layer's outputs).
 __global__ void k_prep_weights(const float* __restrict__ w, float* __restrict__ wt, float* __restrict__ wd) {
-  // one thread per weight element of all layers
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   int64_t off = 0;
-  for (int l = 0; l < LS_NLAYER; ++l) {
-    const int cin = LS_LAYERS[l].cin, cout = LS_LAYERS[l].cout;
-    const int64_t nw = (int64_t)cout * 9 * cin;
-    if (i >= off && i < off + nw) {
-      const int64_t r = i - off;
-      const int co = (int)(r / (9 * cin));
-      const int tap = (int)((r / cin) % 9);
-      const int ci = (int)(r % cin);
-      const float v = w[i];
-      wt[off + ((int64_t)tap * cin + ci) * cout + co] = v;
-      wd[off + ((int64_t)(8 - tap) * cout + co) * cin + ci] = v;
-      return;
+  for (int d = 0; d < (wd ? 2 : 1); ++d) {
+    int64_t woff = 0, dst = 0;
+    for (int l = 0; l < LS_NLAYER; ++l) {
+      const int cin = LS_LAYERS[l].cin, cout = LS_LAYERS[l].cout;
+      const int kin = d ? cout : cin, kout = d ? cin : cout;
+      const int64_t np = ls_conv_f32_packed(kin, kout);
+      if (i < off + np) {
+        int co, tap, ci;
+        ls_conv_f32_element(kin, i - off, co, tap, ci);
+        float v = 0.f;
+        if (co < kout) v = d ? w[woff + ((int64_t)ci * 9 + 8 - tap) * cin + co] : w[woff + ((int64_t)co * 9 + tap) * cin + ci];
+        (d ? wd : wt)[dst + i - off] = v;
+        return;
+      }
+      off += np;
+      dst += np;
+      woff += (int64_t)cout * 9 * cin + cout;
     }
-    off += nw + cout;
   }
 }
 
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-
-// Pixel (yy, xx) of the conv input, channels [c, c+4) of source part `which`.
-template <bool MASK>
-__device__ __forceinline__ float4 src_load4(const ConvSrc& s, int b, int yy, int xx, int c, bool& ok) {
-  const SrcPart& p = c < s.a.c ? s.a : s.b;
-  const int cc = c < s.a.c ? c : c - s.a.c;
-  int sy, sx;
-  if (p.up) {
-    sy = yy >> 1;
-    sx = xx >> 1;
-  } else {
-    sy = yy - p.oy;
-    sx = xx - p.ox;
-  }
-  ok = sy >= 0 && sx >= 0 && sy < p.h && sx < p.w;
-  if (!ok) return make_float4(0.f, 0.f, 0.f, 0.f);
-  const int64_t o = (((int64_t)b * p.h + sy) * p.w + sx) * p.stride + p.coff + cc;
-  float4 v = ld4(p.f32 + o);
-  if (MASK && p.mask) {
-    const float4 m = ld4(p.mask + o);
-    v.x = m.x > 0.f ? v.x : 0.f;
-    v.y = m.y > 0.f ? v.y : 0.f;
-    v.z = m.z > 0.f ? v.z : 0.f;
-    v.w = m.w > 0.f ? v.w : 0.f;
-  }
-  return v;
-}
-
-// Generic FP32 direct conv: out[b][y0+i][x0+j][co] for i < Ho, j < Wo over an
-// H x W input plane with zero padding.
-template <int COB, bool MASK>
-__global__ void __launch_bounds__(CT) k_conv_f32(ConvArgs A) {
-  const int64_t pix = blockIdx.x * (int64_t)CT + threadIdx.x;
-  const int64_t npix = (int64_t)A.B * A.Ho * A.Wo;
-  if (pix >= npix) return;
-  const int b = (int)(pix / ((int64_t)A.Ho * A.Wo));
-  const int r = (int)(pix - (int64_t)b * A.Ho * A.Wo);
-  const int oy = r / A.Wo, ox = r - oy * A.Wo;
-  const int y = A.y0 + oy, x = A.x0 + ox;
-  const int co0 = blockIdx.y * COB;
-  const int cin = A.src.a.c + A.src.b.c;
-  float acc[COB];
-#pragma unroll
-  for (int c = 0; c < COB; ++c) acc[c] = A.bias ? A.bias[co0 + c] : 0.f;
-  for (int ky = 0; ky < 3; ++ky) {
-    const int yy = y + ky - 1;
-    if (yy < 0 || yy >= A.H) continue;
-    for (int kx = 0; kx < 3; ++kx) {
-      const int xx = x + kx - 1;
-      if (xx < 0 || xx >= A.W) continue;
-      const float* wrow = A.wt + (int64_t)(ky * 3 + kx) * cin * A.cout + co0;
-      for (int ci = 0; ci < cin; ci += 4) {
-        bool ok;
-        const float4 v = src_load4<MASK>(A.src, b, yy, xx, ci, ok);
-        if (!ok) continue;
-        const float* w0 = wrow + (int64_t)ci * A.cout;
-#pragma unroll
-        for (int c = 0; c < COB; ++c) {
-          float s = acc[c];
-          s = fmaf(v.x, w0[c], s);
-          s = fmaf(v.y, w0[A.cout + c], s);
-          s = fmaf(v.z, w0[2 * A.cout + c], s);
-          s = fmaf(v.w, w0[3 * A.cout + c], s);
-          acc[c] = s;
-        }
-      }
-    }
-  }
-  float* o = A.out + pix * A.out_stride + A.out_coff + co0;
-#pragma unroll
-  for (int c = 0; c < COB; ++c) o[c] = A.relu ? fmaxf(acc[c], 0.f) : acc[c];
-}
-
-// out = avgpool2x2(in), NHWC, C multiple of 4
-__global__ void k_avgpool_f32(const float* __restrict__ in, float* __restrict__ out, int B, int H, int W, int C) {
-  const int64_t n = (int64_t)B * (H / 2) * (W / 2) * (C / 4);
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int c4 = (int)(i % (C / 4));
-  int64_t r = i / (C / 4);
-  const int x = (int)(r % (W / 2));
-  r /= (W / 2);
-  const int y = (int)(r % (H / 2));
-  const int b = (int)(r / (H / 2));
-  const float* p = in + (((int64_t)b * H + 2 * y) * W + 2 * x) * C + 4 * c4;
-  const float4 a = ld4(p), bq = ld4(p + C), c = ld4(p + (int64_t)W * C), d = ld4(p + (int64_t)W * C + C);
-  float4 o;
-  o.x = 0.25f * ((a.x + bq.x) + (c.x + d.x));
-  o.y = 0.25f * ((a.y + bq.y) + (c.y + d.y));
-  o.z = 0.25f * ((a.z + bq.z) + (c.z + d.z));
-  o.w = 0.25f * ((a.w + bq.w) + (c.w + d.w));
-  reinterpret_cast<float4*>(out)[i] = o;
-}
 
 // Head epilogue: y = crop(x[..., {0,2,3,4}]) + head, texture.
 __global__ void k_head_epilogue(const float* __restrict__ head, const float* __restrict__ x, const double* __restrict__ cz,
@@ -878,38 +790,6 @@ SrcPart src_plain(const float* p, int c, int h, int w, int stride, int coff, con
 
 SrcPart src_none() { return src_plain(nullptr, 0, 0, 0, 0, 0, nullptr); }
 
-int ls_conv_f32(const ConvArgs& a, hipStream_t st) {
-  const int64_t npix = (int64_t)a.B * a.Ho * a.Wo;
-  const bool mask = (a.src.a.mask != nullptr) || (a.src.b.mask != nullptr);
-  const int cap = a.cob_max > 0 ? a.cob_max : 32;
-  int cob = 4;
-  for (int c = 32; c >= 4; c /= 2)
-    if (c <= cap && a.cout % c == 0) {
-      cob = c;
-      break;
-    }
-  if (a.cout % 4) return LS_ENOTIMPL;
-  dim3 grid(nblk(npix), a.cout / cob);
-  LS_TRACE("conv_f32", st);
-#define LS_CONV_CASE(N)                                                                   \
-  if (cob == N) {                                                                          \
-    if (mask) hipLaunchKernelGGL((k_conv_f32<N, true>), grid, dim3(CT), 0, st, a);         \
-    else hipLaunchKernelGGL((k_conv_f32<N, false>), grid, dim3(CT), 0, st, a);             \
-  }
-  LS_CONV_CASE(32) LS_CONV_CASE(16) LS_CONV_CASE(8) LS_CONV_CASE(4)
-#undef LS_CONV_CASE
-  LS_LAUNCH_CHECK();
-  return LS_OK;
-}
-
-int ls_avgpool_f32(const float* in, float* out, int B, int H, int W, int C, hipStream_t st) {
-  const int64_t n = (int64_t)B * (H / 2) * (W / 2) * (C / 4);
-  LS_TRACE("avgpool_f32", st);
-  hipLaunchKernelGGL(k_avgpool_f32, dim3(nblk(n)), dim3(CT), 0, st, in, out, B, H, W, C);
-  LS_LAUNCH_CHECK();
-  return LS_OK;
-}
-
 int ls_head_epilogue(const float* head, const float* x, const double* cz, int B, int res, int pad, double r_m,
                      float* y_out, float* tex_out, hipStream_t st) {
   const int64_t n = (int64_t)B * res * res;
@@ -919,9 +799,18 @@ int ls_head_epilogue(const float* head, const float* x, const double* cz, int B,
   return LS_OK;
 }
 
+int64_t ls_f32_packed_offset(int layer, bool dgrad) {
+  int64_t off = 0;
+  for (int l = 0; l < layer; ++l)
+    off += dgrad ? ls_conv_f32_packed(LS_LAYERS[l].cout, LS_LAYERS[l].cin)
+                 : ls_conv_f32_packed(LS_LAYERS[l].cin, LS_LAYERS[l].cout);
+  return off;
+}
+
 int ls_prep_weights(const float* w, float* wt, float* wd, hipStream_t st) {
   LS_TRACE("prep_weights", st);
-  hipLaunchKernelGGL(k_prep_weights, dim3(nblk(LS_NUM_PARAMS)), dim3(CT), 0, st, w, wt, wd);
+  const int64_t n = ls_f32_packed_offset(LS_NLAYER, false) + (wd ? ls_f32_packed_offset(LS_NLAYER, true) : 0);
+  hipLaunchKernelGGL(k_prep_weights, dim3(nblk(n)), dim3(CT), 0, st, w, wt, wd);
   LS_LAUNCH_CHECK();
   return LS_OK;
 }

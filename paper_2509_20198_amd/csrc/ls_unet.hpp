@@ -25,13 +25,15 @@ struct ConvArgs {
   ConvSrc src;
   int B, H, W;           // batch and input plane (zero padding outside)
   int y0, x0, Ho, Wo;    // output window inside the plane
-  const float* wt;       // [9][cin][cout] weights of this layer
+  const float* wt;       // weights of this layer, packed (ls_conv_f32_element)
   const float* bias;     // [cout] or null
   int cout;
   int relu;
   float* out;            // [B][Ho][Wo][out_stride]
   int out_stride, out_coff;
-  int cob_max;           // largest output-channel block per thread (32, 16, 8 or 4)
+  float* pool_out;       // 2 x 2 average of the output (whole planes only) or null; out may then be null
+  int pool_stride, pool_coff;
+  int tiling;            // 0: by size; 1: 8 x 4 pixels per wave; 2: 8 x 8; 3: 8 x 4 and twice the waves
 };
 
 struct WgradArgs {
@@ -51,8 +53,27 @@ struct WgradArgs {
 
 // Tiling choices per (layer, precision, pass), set by ls_set_conv_config.
 int ls_conv_config_get(int layer, int precision, int pass);
-// FP32 conv: config 0..3 -> channel block cap 32, 16, 8, 4
-inline int ls_cob_for_config(int c) { return c <= 0 ? 32 : (c == 1 ? 16 : (c == 2 ? 8 : 4)); }
+// FP32 conv: config 0..3 -> ConvArgs::tiling
+inline int ls_f32_tiling_for_config(int c) { return c < 0 ? 0 : (c & 3); }
+
+// Packed FP32 conv weights: [channel tile of 16][tap][block of KB input
+// channels][lane][KB / 4], lane l holding output channel l % 16 at input
+// channels l / 16 + 4 s, s = 0, 1, .. of the block; channels beyond cout are
+// zero.
+__host__ __device__ inline int ls_conv_f32_block(int cin) { return cin % 16 == 0 ? 16 : (cin % 8 == 0 ? 8 : 4); }
+__host__ __device__ inline int64_t ls_conv_f32_packed(int cin, int cout) {
+  return (int64_t)((cout + 15) / 16) * 16 * 9 * cin;
+}
+// (output channel, tap, input channel) of packed element r
+__host__ __device__ inline void ls_conv_f32_element(int cin, int64_t r, int& co, int& tap, int& ci) {
+  const int kb = ls_conv_f32_block(cin), v = kb / 4;
+  const int s = (int)(r % v), lane = (int)((r / v) % 64);
+  const int64_t blk = r / (v * 64);
+  const int nblk = cin / kb, j = (int)(blk % nblk);
+  tap = (int)((blk / nblk) % 9);
+  co = (int)(blk / nblk / 9) * 16 + (lane & 15);
+  ci = j * kb + 4 * s + (lane >> 4);
+}
 // weight gradient: config 0..2 -> pixel chunks 512, 256, 128 (vector FP32
 // products); BF16 also 3..5 -> the same chunk counts on the matrix cores
 inline int ls_wgrad_chunks_for_config(int c) {
@@ -64,9 +85,11 @@ SrcPart src_plain(const float* p, int c, int h, int w, int stride, int coff, con
 SrcPart src_none();
 
 int ls_conv_f32(const ConvArgs& a, hipStream_t st);
-int ls_avgpool_f32(const float* in, float* out, int B, int H, int W, int C, hipStream_t st);
 int ls_head_epilogue(const float* head, const float* x, const double* cz, int B, int res, int pad, double r_m,
                      float* y_out, float* tex_out, hipStream_t st);
+// packed weights of the U-Net's layers for the forward (wt) and the input
+// gradients (wd: 180-degree turned, transposed; null to skip)
+int64_t ls_f32_packed_offset(int layer, bool dgrad);  // layer LS_NLAYER: the total
 int ls_prep_weights(const float* w, float* wt, float* wd, hipStream_t st);
 int ls_wgrad_f32(const WgradArgs& a, float* grad_w_layer, hipStream_t st);
 int ls_up_adjoint(const float* dhigh, int stride, float* dlow, int B, int h, int w, int c_low, hipStream_t st);
