@@ -74,9 +74,9 @@ __global__ void k_head_epilogue(const float* __restrict__ head, const float* __r
 // ---------------------------------------------------------------- backward
 // dW partials as a register-tiled product: dW[co][n] = sum over pixels of
 // dZ(p, co) * I(p, n), with n = tap*cin + ci the im2col column and column
-// n = 9*cin standing for the bias (I = 1).  dZ(p, co) = dA[p][co] masked by
-// A[p][co] > 0 (or a pre-masked BF16 copy), defined on the output window;
-// I is read through the forward ConvSrc.  A workgroup owns one pixel chunk
+// n = 9*cin standing for the bias (I = 1).  dZ(p, co) is the masked BF16
+// gradient, defined on the output window; I is read through the forward
+// ConvSrc.  A workgroup owns one pixel chunk
 // (blockIdx.y) and WG_COLS columns (blockIdx.x) for all output channels;
 // slabs of WG_KP pixels are staged in LDS and every thread accumulates a
 // 4x4 block (4 channels x 4 columns) in FP32, in a fixed order.
@@ -142,18 +142,7 @@ __global__ void __launch_bounds__(CT) k_wgrad_tiled(WgradArgs A) {
       float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
       if (p < p1 && 4 * c4 < A.cout) {
         const int64_t o = p * A.d_stride + 4 * c4;
-        if (A.g_bf16) {
-          g = bf16x4_to_f32(*reinterpret_cast<const uint2*>(A.g_bf16 + o));
-        } else {
-          g = *reinterpret_cast<const float4*>(A.dA + o);
-          if (A.mask) {
-            const float4 m = *reinterpret_cast<const float4*>(A.mask + o);
-            g.x = m.x > 0.f ? g.x : 0.f;
-            g.y = m.y > 0.f ? g.y : 0.f;
-            g.z = m.z > 0.f ? g.z : 0.f;
-            g.w = m.w > 0.f ? g.w : 0.f;
-          }
-        }
+        g = bf16x4_to_f32(*reinterpret_cast<const uint2*>(A.g_bf16 + o));
       }
       s_g[kk][c4] = g;
     }
@@ -823,6 +812,7 @@ int ls_wgrad_f32(const WgradArgs& a, float* grad_w_layer, hipStream_t st) {
   const int mwg = a.cout <= 16 ? 16 : (a.cout <= 32 ? 32 : 64);
   if (a.cout > 64) return LS_ENOTIMPL;
   LS_TRACE("wgrad", st);
+  int nchunk = a.nchunk;
   // the tile kernel: 16 x 16 output tiles, the input staged once per tile
   if (a.mfma == 2 && a.g_bf16 && a.src.a.c % 8 == 0 && a.src.b.c % 8 == 0 && a.cout <= 32 && a.d_stride % 4 == 0) {
     const int ng8 = cin / 8;
@@ -864,6 +854,9 @@ int ls_wgrad_f32(const WgradArgs& a, float* grad_w_layer, hipStream_t st) {
       if (ctw == 2) LS_WM(4, 2); else if (ctw == 4) LS_WM(4, 4); else LS_WM(4, 8);
     }
 #undef LS_WM
+  } else if (!a.g_bf16) {
+    const int rc = ls_wgrad_f32_partials(a, &nchunk, st);
+    if (rc != LS_OK) return rc;
   } else {
     const int cols = 4 * (CT / (mwg / 4));
     dim3 grid((unsigned)((9 * cin + 1 + cols - 1) / cols), (unsigned)a.nchunk);
@@ -874,7 +867,7 @@ int ls_wgrad_f32(const WgradArgs& a, float* grad_w_layer, hipStream_t st) {
     }
   }
   hipLaunchKernelGGL(k_reduce_partials, dim3((unsigned)((n + RED_OUT - 1) / RED_OUT)), dim3(CT), 0, st, a.partial,
-                     a.nchunk, n, grad_w_layer);
+                     nchunk, n, grad_w_layer);
   LS_LAUNCH_CHECK();
   return LS_OK;
 }

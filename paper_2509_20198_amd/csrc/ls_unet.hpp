@@ -74,8 +74,8 @@ __host__ __device__ inline void ls_conv_f32_element(int cin, int64_t r, int& co,
   co = (int)(blk / nblk / 9) * 16 + (lane & 15);
   ci = j * kb + 4 * s + (lane >> 4);
 }
-// weight gradient: config 0..2 -> pixel chunks 512, 256, 128 (vector FP32
-// products); BF16 also 3..5 -> the same chunk counts on the matrix cores
+// weight gradient: config 0..2 -> 512, 256, 128 chunks of partial sums (FP32:
+// on the matrix cores; BF16: vector FP32 products, 3..5 on the matrix cores)
 inline int ls_wgrad_chunks_for_config(int c) {
   const int k = c < 0 ? 0 : c % 3;
   return k == 0 ? 512 : (k == 1 ? 256 : 128);
@@ -92,6 +92,7 @@ int ls_head_epilogue(const float* head, const float* x, const double* cz, int B,
 int64_t ls_f32_packed_offset(int layer, bool dgrad);  // layer LS_NLAYER: the total
 int ls_prep_weights(const float* w, float* wt, float* wd, hipStream_t st);
 int ls_wgrad_f32(const WgradArgs& a, float* grad_w_layer, hipStream_t st);
+int ls_wgrad_f32_partials(const WgradArgs& a, int* nchunk, hipStream_t st);
 int ls_up_adjoint(const float* dhigh, int stride, float* dlow, int B, int h, int w, int c_low, hipStream_t st);
 int ls_copy_channels(const float* src, int stride, int coff, float* dst, int C, int64_t npix, int acc, hipStream_t st);
 // dst [B][H][H][C] += src, the window tensor [B][n][n][C] of the pixels [y0, y0 + n)^2
