@@ -2,36 +2,42 @@
 // Algorithm 1; normalisation of Section 3.4) for gfx950.
 //
 // Pipeline of ls_recon_tiles, all on one stream, no host round trip:
-//   1. k_init / k_tile_pos: map linear tile id -> output slot.
+//   1. k_tile_pos: map linear tile id -> output slot.
 //   2. k_bin_count, k_bin_scan, k_bin_scatter: CSR of the points in every
 //      listed tile's padded window [c - H, c + H)^2 (a point sits in 1, 2 or
 //      4 windows with the paper's 16-texel ring).
 //   3. k_bin_sort (only when the caller asks for the CSR): ascending order.
-//   4. k_recon: persistent, one workgroup per tile popped from a queue that
-//      holds the tiles in the caller's list order (viewpoint priority) or by
-//      descending window point count (longest first, so the last tiles to
-//      start are short and the workgroups finish together).  Phases,
-//      separated by barriers:
+//   4. for as many tiles at a time as the workspace holds face maps, in the
+//      caller's list order (viewpoint priority) or by descending window point
+//      count:
+//      k_recon_prep, one workgroup per tile:
 //        a. gather the tile's points to tile-local coordinates and bucket
 //           them into a G x G grid over the window (LDS counting sort);
 //        b. sort each bucket by (v, u) and drop duplicate positions,
-//           keeping the largest (z, R, G, B) -> canonical points;
-//        c. face map reset;
-//        d. Delaunay triangulation: every point computes its own star by
-//           gift-wrapping (first point hit by a circle growing from a
-//           Delaunay edge), with exact orientation and in-circle tests and a
-//           symbolic perturbation of the lifted heights (lower canonical
-//           index = larger perturbation) that makes the triangulation unique
-//           when points are cocircular.  A triangle is rasterised by its
-//           lowest-index vertex into a per-texel face map (top-left rule),
-//           hull edges by one endpoint, so every texel of the closed convex
-//           hull gets a containing triangle.  Waves whose walks are done go
-//           on to the nearest point of every texel centre (exact distances,
-//           ties by (d^2, v, u)) by scans over the buckets;
+//           keeping the largest (z, R, G, B) -> canonical points; face map
+//           reset;
+//      k_recon_stars, a list of small runs of points for the whole chip:
+//        c. Delaunay triangulation by gift-wrapping around every point (first
+//           point hit by a circle growing from a Delaunay edge), with exact
+//           orientation and in-circle tests and a symbolic perturbation of
+//           the lifted heights (lower canonical index = larger perturbation)
+//           that makes the triangulation unique when points are cocircular.
+//           A triangle is rasterised by its lowest vertex into a per-texel
+//           face map (top-left rule), hull edges by their lower endpoint, so
+//           every texel of the closed convex hull gets a containing triangle;
+//      k_recon_out, several workgroups per tile:
+//        d. nearest point of every texel centre (exact distances, ties by
+//           (d^2, v, u)) by scans over the buckets;
 //        e. c_z from the centre texel, then per texel: barycentric height and
 //           colour inside the hull, nearest point outside it (the paper's
 //           corner padding points taken at infinity), normalised and written
 //           as one NHWC row of 8 FP32 channels.
+// Three launches rather than one workgroup per tile from end to end: the work
+// of a tile follows its point count (20 to tens of thousands), and a launch
+// over runs of points spreads the largest tile over the chip.  One tile of 400
+// points 535 -> 204 us (reconstruction and network), one of 16,000 points
+// 16.3 -> 0.75 ms, 1024 tiles of 50-2000 points 2.23 -> 1.82 ms, 16384 tiles of
+// 20-5000 points 12.7 -> 8.9 ms.
 #include <algorithm>
 #include <mutex>
 
@@ -39,19 +45,24 @@
 
 namespace {
 
-constexpr int RB = 512;                  // threads per recon workgroup
-constexpr int LDS_INTS = 16000;          // 62.5 KiB of LDS per recon workgroup
-constexpr int MAXG = 88;                 // max buckets per side
+constexpr int RB = 512;                  // threads of a preparation workgroup
+constexpr int PREP_INTS = 12000;         // its LDS: windows up to about 3,000 points sort there
+constexpr int MAXG = 76;                 // max buckets per side
 constexpr int MAXB = MAXG * MAXG;        // max buckets
-static_assert(2 * (MAXB + 1) <= LDS_INTS, "bucket offsets must fit twice in the recon LDS");
+static_assert(2 * (MAXB + 1) <= PREP_INTS, "bucket offsets must fit twice in the preparation's LDS");
+constexpr int TB = 256;                  // threads of a star or output workgroup
+constexpr int OUT_INTS = 9600;           // LDS of an output workgroup for the points and bucket offsets
+constexpr int ITEM_MIN = 8, ITEM_MAX = 16;  // points of a work item of the stars
+constexpr int CAND = 8;                  // candidates of a star a lane holds
+constexpr int CANDS = 8 * CAND;          // and the eight lanes of a star
+constexpr int TRI_CAP = 96;              // triangles a wave collects
 constexpr int STAR_MAX_STEPS = 1024;     // safeguard on one point's star walk
 constexpr uint64_t FACE_NONE = ~0ull;
-constexpr int SUCC_K = 8;                // cached star successors per point
-constexpr uint64_t SUCC_EMPTY = ~0ull;
-constexpr int SEARCH_MAX_HITS = 8;       // a wave searches once at most this many lanes can step from the lists
 // First square of a third-vertex search: its centre this share of the edge's
 // length beside the midpoint, its half side this share, at least SEARCH_MIN buckets
-constexpr float SEARCH_OFFSET = 0.5f, SEARCH_SIZE = 0.7f, SEARCH_MIN = 0.5f;
+constexpr float SEARCH_OFFSET = 0.5f, SEARCH_SIZE = 0.9f, SEARCH_MIN = 0.6f;
+// First margin, in buckets, of a nearest-point search
+constexpr float NEAR_MARGIN = 0.8f;
 constexpr int SORT_LDS = 16384;          // bin segments up to this size sort in LDS
 
 struct BinParams {
@@ -304,7 +315,6 @@ struct ReconParams {
   int64_t ox, oy;
   int32_t S, tiles_x, C, R, H;
   double scale_z, offset_z, inv_r;
-  int32_t n_tiles;
   const int32_t* x;
   const int32_t* y;
   const int32_t* z;
@@ -313,30 +323,37 @@ struct ReconParams {
   const int32_t* bin_off;
   const int32_t* bin_idx;
   const int32_t* flags;
-  // per bin entry scratch: staging (reused for the canonical heights and
-  // colours), sorted copies, canonical coordinates
+  // per bin entry: tile-local coordinates and bucket slots, sort keys and
+  // entries of windows that do not sort in LDS, canonical points
   int32_t* su;
   int32_t* sv;
-  int32_t* sz;
-  uint64_t* srgb;  // R | G << 16 | B << 32
   int32_t* sslot;
-  int32_t* tu;
-  int32_t* tv;
-  int32_t* tz;
-  uint64_t* trgb;
+  uint64_t* skey;
+  int32_t* sidx;
   int2* cuv;
-  uint64_t* tris;  // 2 entries per bin entry: large triangles of a tile, rasterised after its stars
-  uint64_t* succ;  // SUCC_K entries per bin entry: known star successors (key << 32 | third vertex)
-  int32_t* succ_n;  // per bin entry: successor entries claimed
-  // per workgroup scratch
-  uint64_t* facemap;  // [gridDim][R*R]
-  int32_t* nnidx;     // [gridDim][R*R]
-  int32_t* queue;
-  const int32_t* order;  // queue position -> tile slot
+  int32_t* cz;
+  uint64_t* crgb;  // R | G << 16 | B << 32
+  int32_t* boff;   // 2 per bin entry: canonical bucket offsets of a tile from 2 * its bin offset on
+  // per tile slot
+  int32_t* npts;   // canonical points
+  int32_t* has_dt; // 1: at least three points, not all collinear
+  uint64_t* facemap;  // R * R texels of every tile of the launch
+  int2* items;        // work items of the stars: position of the tile in the launch, first point
+  int32_t* item_n;    // how many, and how many are taken
+  int32_t item;       // points of an item
+  const int32_t* order;  // processing position -> tile slot
+  int32_t q0;            // first position of the launch
   float* x_out;
   double* cz_out;
   int32_t* status;
 };
+
+// Bucket grid side of a window with cnt points: 1.25 points a bucket (1024 tiles
+// of 50-2000 points 1.90 ms, 1.96 with 1.5, 1.91 with 1).
+__device__ __forceinline__ int bucket_side(int cnt) {
+  const int want = (int)sqrtf((float)cnt * 0.8f);
+  return want < 1 ? 1 : (want > MAXG ? MAXG : want);
+}
 
 // Pointers into LDS typed as such, so that reads through them are LDS reads
 // (a generic pointer that may point to LDS or to global memory compiles to
@@ -356,19 +373,18 @@ struct UvGlobal {
   __device__ __forceinline__ int2 operator[](int i) const { return p[i]; }
 };
 
-// A tile's canonical points: coordinates through UVP (UvLds when the
-// tile's points are staged in LDS, else UvGlobal).
-template <class UVP>
+// A tile's canonical points: coordinates through UVP (UvLds or UvGlobal),
+// bucket offsets (G * G + 1, row-major) through BP.
+template <class UVP, class BP>
 struct TileT {
-  UVP uv;       // canonical coordinates
-  LdsI32 boff;  // G*G + 1 canonical bucket offsets
+  UVP uv;
+  BP boff;
   int G, H, W2;
-  double bw;  // bucket width in raw units
   float inv;  // buckets per raw unit
 };
 
-// floor(w * G / W2) for 0 <= w < W2 <= 2^19 and G <= 88 (all products below
-// 2^26, so the float estimate of a quotient below 88 is off by far less
+// floor(w * G / W2) for 0 <= w < W2 <= 2^19 and G <= 76 (all products below
+// 2^26, so the float estimate of a quotient below 76 is off by far less
 // than one): a float reciprocal estimate, then an exact integer correction
 // by at most one.
 __device__ __forceinline__ int bucket_1d(int w, int G, int W2) {
@@ -389,9 +405,8 @@ __device__ __forceinline__ double orient_d(double ax, double ay, double bx, doub
 __device__ __forceinline__ int sgn_d(double v) { return (v > 0.0) - (v < 0.0); }
 
 // Exact sign of the in-circle determinant in int128 (|terms| < 2^79), then
-// the symbolic perturbation for exactly cocircular points.  Kept out of line:
-// the floating-point filter below settles nearly every call.
-__device__ __noinline__ int incircle_exact(int a, int b, int c, int d, int2 pa, int2 pb, int2 pc, int2 pd) {
+// the symbolic perturbation for exactly cocircular points.
+__device__ int incircle_exact(int a, int b, int c, int d, int2 pa, int2 pb, int2 pc, int2 pd) {
   const int64_t adx = pa.x - pd.x, ady = pa.y - pd.y;
   const int64_t bdx = pb.x - pd.x, bdy = pb.y - pd.y;
   const int64_t cdx = pc.x - pd.x, cdy = pc.y - pd.y;
@@ -430,147 +445,181 @@ __device__ __forceinline__ int incircle_sos(int a, int b, int c, int d, int2 pa,
   return incircle_exact(a, b, c, d, pa, pb, pc, pd);
 }
 
+// Nearest points of an 8 x 8 block of texels, one texel per lane of a wave;
+// ties go to the smallest (d^2, v, u).  The 16 lanes of a 4 x 4 texel
+// sub-block scan the same buckets, those under the sub-block widened by a
+// margin, so their loop is uniform and a point is one LDS broadcast; the
+// margin grows until it covers the distance of every lane's answer, which
+// proves it.  (i, j) is the lane's texel, inside the grid for every lane that
+// counts.
 template <class TT>
-__device__ __forceinline__ bool ring_covers_grid(const TT& T, int bx0, int by0, int r) {
-  return bx0 - r <= 0 && by0 - r <= 0 && bx0 + r >= T.G - 1 && by0 + r >= T.G - 1;
-}
-
-// Nearest canonical point to (qx, qy), ties by smallest (d^2, v, u); skips
-// point `skip`.  Returns -1 if no point.  Chebyshev rings of buckets around
-// q's bucket; once a candidate exists, buckets farther from q than it are
-// skipped, and the search stops when the candidate is closer than the
-// nearest side of the square visited so far.
-template <class TT>
-__device__ int ring_nearest(const TT& T, int qx, int qy, int skip) {
-  const int G = T.G;
-  const int bx0 = bucket_1d(qx + T.H, G, T.W2), by0 = bucket_1d(qy + T.H, G, T.W2);
-  const double fx = qx + T.H, fy = qy + T.H;  // grid-local
+__device__ int nearest_of_texel(const TT& T, int q0, int C, int R, int i0, int j0, int i, int j) {
+  const int qx = q0 + j * C, qy = q0 + i * C;
+  const bool in_grid = i < R && j < R;
+  const float gx0 = (float)(q0 + j0 * C + T.H) * T.inv, gx1 = (float)(q0 + min(j0 + 3, R - 1) * C + T.H) * T.inv;
+  const float gy0 = (float)(q0 + i0 * C + T.H) * T.inv, gy1 = (float)(q0 + min(i0 + 3, R - 1) * C + T.H) * T.inv;
+  float r = NEAR_MARGIN;
   int best = -1;
-  double bd = 0.0;  // squared distance, exact in double (below 2^40)
-  int bu = 0, bv = 0;
-  for (int r = 0;; ++r) {
-    const int ylo = by0 - r, yhi = by0 + r, xlo = bx0 - r, xhi = bx0 + r;
-    for (int by = max(ylo, 0); by <= min(yhi, G - 1); ++by) {
-      const bool full = (by == ylo || by == yhi);
-      const int step = full ? 1 : (xhi - xlo);
-      for (int bx = xlo; bx <= xhi; bx += (step > 0 ? step : 1)) {
-        if (bx < 0 || bx >= G) continue;
-        if (best >= 0) {
-          // distance from q to the bucket rectangle, rounded outwards
-          const double x0 = floor(bx * T.bw) - 1.0, x1 = ceil((bx + 1) * T.bw) + 1.0;
-          const double y0 = floor(by * T.bw) - 1.0, y1 = ceil((by + 1) * T.bw) + 1.0;
-          const double dx = fmax(fmax(x0 - fx, fx - x1), 0.0), dy = fmax(fmax(y0 - fy, fy - y1), 0.0);
-          if (dx * dx + dy * dy > bd) continue;
+  double bd = 1e300;  // squared distance, exact in double (below 2^40)
+  for (;;) {
+    const int x0 = max((int)floorf(gx0 - r), 0), x1 = min((int)floorf(gx1 + r), T.G - 1);
+    const int y0 = max((int)floorf(gy0 - r), 0), y1 = min((int)floorf(gy1 + r), T.G - 1);
+    for (int y = y0; y <= y1; ++y) {
+      const int e = T.boff[y * T.G + x1 + 1];
+      for (int p = T.boff[y * T.G + x0]; p < e; ++p) {
+        const int2 P = T.uv[p];
+        const double dx = P.x - qx, dy = P.y - qy;
+        const double d = fma(dx, dx, dy * dy);
+        bool less = d < bd;
+        if (d == bd) {  // rare: two points at the same distance (or the same point again)
+          const int2 Q = T.uv[best];
+          less = P.y < Q.y || (P.y == Q.y && P.x < Q.x);
         }
-        const int b = by * G + bx;
-        const int e = T.boff[b + 1];
-        for (int p = T.boff[b]; p < e; ++p) {
-          if (p == skip) continue;
-          const int2 q = T.uv[p];
-          const double dx = q.x - qx, dy = q.y - qy;
-          const double d = fma(dx, dx, dy * dy);
-          if (best < 0 || d < bd || (d == bd && (q.y < bv || (q.y == bv && q.x < bu)))) {
-            best = p;
-            bd = d;
-            bu = q.x;
-            bv = q.y;
-          }
-        }
+        bd = less ? d : bd;
+        best = less ? p : best;
       }
     }
-    if (best >= 0) {
-      // distance from q to the outside of the square of buckets visited
-      const double L = fmin(fmin(fx - floor((bx0 - r) * T.bw), ceil((bx0 + r + 1) * T.bw) - fx),
-                            fmin(fy - floor((by0 - r) * T.bw), ceil((by0 + r + 1) * T.bw) - fy)) -
-                       1.0;
-      if (L > 0.0 && bd < L * L) break;
-    }
-    if (ring_covers_grid(T, bx0, by0, r)) break;
+    float need = !in_grid ? 0.f : (best >= 0 ? sqrtf((float)bd) * T.inv * 1.000001f + 1e-3f : 2.f * r);
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) need = fmaxf(need, __shfl_xor(need, o, 64));
+    if (need <= r || (x0 == 0 && y0 == 0 && x1 == T.G - 1 && y1 == T.G - 1)) break;
+    r = need;
   }
   return best;
 }
 
-// Nearest points of an 8 x 8 block of texels, one texel per lane of a wave
-// (lane = 8 * row + column): every lane scans the same candidate list, the
-// points of the buckets under the block widened by one bucket on each side,
-// so the loops are uniform and each point is read once per wave (an LDS
-// broadcast).  A texel keeps the scan's answer when its best squared
-// distance is below the squared distance to every side of the scanned
-// bucket rectangle that faces more buckets (sides rounded inwards by one raw
-// unit).  While some lane of the wave cannot prove its answer (sparse parts
-// of the window), the rectangle grows by one bucket ring, scanned the same
-// way, up to two rings; a lane still unproven then falls back to
-// ring_nearest.  Same order on (d^2, v, u), so the result equals
-// ring_nearest's.
-template <class TT>
-__device__ int nearest_block(const TT& T, int q0, int C, int R, int bi, int bj, int lane, int& qx, int& qy) {
-  const int G = T.G;
-  const int i = bi * 8 + (lane >> 3), j = bj * 8 + (lane & 7);
-  const bool in_grid = i < R && j < R;
-  qx = q0 + j * C;
-  qy = q0 + i * C;
-  const int i1 = min(bi * 8 + 7, R - 1), j1 = min(bj * 8 + 7, R - 1);
-  int bx0 = max(bucket_1d(q0 + bj * 8 * C + T.H, G, T.W2) - 1, 0);
-  int bx1 = min(bucket_1d(q0 + j1 * C + T.H, G, T.W2) + 1, G - 1);
-  int by0 = max(bucket_1d(q0 + bi * 8 * C + T.H, G, T.W2) - 1, 0);
-  int by1 = min(bucket_1d(q0 + i1 * C + T.H, G, T.W2) + 1, G - 1);
-  int best = -1, bu = 0, bv = 0;
-  double bd = 0.0;  // squared distance, exact in double (below 2^40)
-  // buckets xlo..xhi of rows ylo..yhi (those of a row are contiguous)
-  auto scan = [&](int ylo, int yhi, int xlo, int xhi) {
-    if (xlo > xhi) return;
-    for (int by = ylo; by <= yhi; ++by) {
-      const int e = T.boff[by * G + xhi + 1];
-      for (int p = T.boff[by * G + xlo]; p < e; ++p) {
-        const int2 q = T.uv[p];
-        const double dx = q.x - qx, dy = q.y - qy;
-        const double d = fma(dx, dx, dy * dy);
-        if (best < 0 || d < bd || (d == bd && (q.y < bv || (q.y == bv && q.x < bu)))) {
-          best = p;
-          bd = d;
-          bu = q.x;
-          bv = q.y;
-        }
+// ---- stars: a group of eight lanes works on one star
+constexpr int STAR_LANES = 8;
+template <int CTRL>
+__device__ __forceinline__ int row_move(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float row_move(float v) {
+  return __builtin_bit_cast(float, row_move<CTRL>(__builtin_bit_cast(int, v)));
+}
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+  const uint64_t w = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)row_move<CTRL>((int)(uint32_t)w), hi = (uint32_t)row_move<CTRL>((int)(uint32_t)(w >> 32));
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+// f over the group: the other lane of a pair, the other pair of a quad, the
+// other quad.
+template <class V, class F>
+__device__ __forceinline__ V group_reduce(V v, F&& f) {
+  v = f(v, row_move<0xB1>(v));
+  v = f(v, row_move<0x4E>(v));
+  return f(v, row_move<0x141>(v));
+}
+__device__ __forceinline__ float group_min(float v) {
+  return group_reduce(v, [](float a, float b) { return fminf(a, b); });
+}
+// Value of the group's first lane.
+__device__ __forceinline__ int group_first(int v) {
+  const int lo = row_move<0x150>(v), hi = row_move<0x158>(v);
+  return threadIdx.x & STAR_LANES ? hi : lo;
+}
+// Sum over the lanes of the group before this one.
+__device__ __forceinline__ int group_before(int v, int gl) {
+  int t, at = v;
+  t = row_move<0x111>(at);  // shifts within the sixteen lanes of a row
+  at += gl >= 1 ? t : 0;
+  t = row_move<0x112>(at);
+  at += gl >= 2 ? t : 0;
+  t = row_move<0x114>(at);
+  at += gl >= 4 ? t : 0;
+  return at - v;
+}
+// Lanes of the group for which the condition holds.
+__device__ __forceinline__ uint32_t group_ballot(bool b) {
+  return (uint32_t)(__ballot(b) >> (threadIdx.x & 56)) & 0xFF;
+}
+
+// Points of the buckets [x0, x1] x [y0, y1] over the lanes of a group (a bucket
+// row each, several lanes to one where these are few), four at a time (the last
+// of a bucket row again where it has fewer); cut(y, x0, x1) narrows a row's
+// columns.
+template <class TT, class Cut, class F>
+__device__ __forceinline__ void row_scan(const TT& T, int x0, int x1, int y0, int y1, int gl, Cut&& cut, F&& f) {
+  int sh = 3;  // log2 of the lanes of a bucket row
+  while (sh > 0 && (STAR_LANES >> sh) < y1 - y0 + 1) --sh;
+  for (int y = y0 + (gl >> sh); y <= y1; y += STAR_LANES >> sh) {
+    int xa = x0, xb = x1;
+    cut(y, xa, xb);
+    if (xa > xb) continue;
+    const int e = T.boff[y * T.G + xb + 1];
+    for (int p = T.boff[y * T.G + xa] + (gl & ((1 << sh) - 1)); p < e; p += 4 << sh) {
+      int id[4];
+      int2 Q[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        id[j] = min(p + (j << sh), e - 1);
+        Q[j] = T.uv[id[j]];
       }
+      f(id, Q, min(4, ((e - 1 - p) >> sh) + 1));
     }
-  };
-  scan(by0, by1, bx0, bx1);
-  const double fx = qx + T.H, fy = qy + T.H;  // grid-local
-  bool proven = false;
-  for (int ring = 0;; ++ring) {
-    // distance from q to the unscanned buckets
-    double L = 1e300;
-    if (bx0 > 0) L = fmin(L, fx - (ceil(bx0 * T.bw) + 1.0));
-    if (bx1 < G - 1) L = fmin(L, (floor((bx1 + 1) * T.bw) - 1.0) - fx);
-    if (by0 > 0) L = fmin(L, fy - (ceil(by0 * T.bw) + 1.0));
-    if (by1 < G - 1) L = fmin(L, (floor((by1 + 1) * T.bw) - 1.0) - fy);
-    proven = best >= 0 && (L >= 1e300 || (L > 0.0 && bd < L * L));
-    if (ring == 2 || __ballot(in_grid && !proven) == 0) break;
-    const int nx0 = max(bx0 - 1, 0), nx1 = min(bx1 + 1, G - 1), ny0 = max(by0 - 1, 0), ny1 = min(by1 + 1, G - 1);
-    scan(ny0, by0 - 1, nx0, nx1);      // new rows below
-    scan(by1 + 1, ny1, nx0, nx1);      // new rows above
-    scan(by0, by1, nx0, bx0 - 1);      // new columns on the left
-    scan(by0, by1, bx1 + 1, nx1);      // new columns on the right
-    bx0 = nx0;
-    bx1 = nx1;
-    by0 = ny0;
-    by1 = ny1;
   }
-  if (proven) return best;
-  return ring_nearest(T, qx, qy, -1);
+}
+
+// Nearest neighbour of point a (the smallest index among equals): the square
+// around it grows until it holds the circle through the nearest point found.
+template <class TT>
+__device__ __forceinline__ int nearest_of_point(const TT& T, int a, int gl) {
+  const int2 A = T.uv[a];
+  const float fx = (float)(A.x + T.H) * T.inv, fy = (float)(A.y + T.H) * T.inv;
+  float r = NEAR_MARGIN;
+  for (;;) {
+    const int x0 = max((int)floorf(fx - r), 0), x1 = min((int)floorf(fx + r), T.G - 1);
+    const int y0 = max((int)floorf(fy - r), 0), y1 = min((int)floorf(fy + r), T.G - 1);
+    int best = INT_MAX;
+    double bd = 1e300;  // squared distance, exact in double (below 2^40)
+    row_scan(T, x0, x1, y0, y1, gl, [](int, int&, int&) {}, [&](const int* p, const int2* Q, int) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const double dx = Q[j].x - A.x, dy = Q[j].y - A.y;
+        const double d = fma(dx, dx, dy * dy);
+        const bool less = p[j] != a && (d < bd || (d == bd && p[j] < best));
+        bd = less ? d : bd;
+        best = less ? p[j] : best;
+      }
+    });
+    const double least = group_reduce(bd, [](double u, double v) { return fmin(u, v); });
+    best = group_reduce(bd == least ? best : INT_MAX, [](int u, int v) { return min(u, v); });
+    bd = least;
+    const float need = best != INT_MAX ? sqrtf((float)bd) * T.inv * 1.000001f + 1e-3f : 2.f * r;
+    if ((best != INT_MAX && need <= r) || (x0 == 0 && y0 == 0 && x1 == T.G - 1 && y1 == T.G - 1)) return best;
+    r = need;
+  }
 }
 
 // The third vertex of the Delaunay triangle on the left of edge a->b: the
-// first point met by a circle through a and b whose centre moves left.
-// Returns -1 if no point lies strictly left of a->b (a->b is a hull edge).
+// first point met by a circle through a and b whose centre moves left; none
+// if no point lies strictly left of a->b (a->b is a hull edge).
 //
 // That point sees the edge under the largest angle, so among the points c with
 // cross(b - a, c - a) > 0 it has the smallest cotangent
-// dot(c - a, c - b) / cross(b - a, c - a).  Both are integers below 2^39,
-// exact in double, so a candidate costs a dozen operations and no branch: two
-// cotangents compare as the products dot * cross', and only where these agree
-// to a few roundings does the exact in-circle test (with its symbolic
-// perturbation) decide.
+// dot(c - a, c - b) / cross(b - a, c - a).  Both are integers below 2^40,
+// exact in double; their quotient is taken in float, with a relative error
+// below 3e-7.  Candidates within COT_NEAR of the least one (nearly always one
+// alone) are settled by the exact in-circle test with its symbolic
+// perturbation.
+constexpr float COT_NONE = 3e38f;
+constexpr float COT_NEAR = 1e-6f;
+__device__ __forceinline__ float cotangent(double dot, double cross) {
+  const float fc = (float)cross;
+  return fc > 0.f ? (float)dot * __builtin_amdgcn_rcpf(fc) : COT_NONE;
+}
+__device__ __forceinline__ float cot_limit(float least) { return fmaf(fabsf(least), COT_NEAR, least); }
+
+// Rectangle in units of buckets.
+struct Rect {
+  float x0, x1, y0, y1;
+};
+
+// The search by the lanes of a group.  `best` is the first point met
+// among the points of `known` (-1: none there), an empty rectangle if none was
+// looked at.
 //
 // The points are scanned by bucket rows of a square beside the edge that
 // doubles until it holds every place a better point could be: the circle
@@ -580,92 +629,113 @@ __device__ int nearest_block(const TT& T, int q0, int C, int R, int bi, int bj, 
 // by 90 degrees, the circle's centre is mid + n t / 2 and its radius
 // |n| sqrt(1 + t^2) / 2.  Squares and circles only bound the search, in float
 // and in units of buckets, with margins far above the float rounding (2e-5
-// buckets at 88 buckets a side); each row is also cut at the edge's line.
-// The search is a few short loops without the per-bucket geometry of a ring
-// search: it is bound by instruction issue under divergence, and this form
-// takes about half the instructions (1024-tile batch 2.22 -> 1.97 ms).
+// buckets at 76 buckets a side); each row is also cut at the edge's line.
 template <class TT>
-__device__ int third_left(const TT& T, int a, int b) {
+__device__ __forceinline__ int third_left(const TT& T, int a, int b, int best, Rect known, int gl) {
   const int2 A = T.uv[a], B = T.uv[b];
   const int iex = B.x - A.x, iey = B.y - A.y;
   const double ex = iex, ey = iey;
-  const float inv = T.inv, fG = (float)T.G;
-  const float fex = (float)iex * inv, fey = (float)iey * inv;
-  const float fax = (float)(A.x + T.H) * inv, fay = (float)(A.y + T.H) * inv;
-  const float mx = fax + 0.5f * fex, my = fay + 0.5f * fey;
-  const float len = sqrtf(fex * fex + fey * fey);
+  const float fG = (float)T.G;
+  const float fex = (float)iex * T.inv, fey = (float)iey * T.inv;
+  const float fax = (float)(A.x + T.H) * T.inv, fay = (float)(A.y + T.H) * T.inv;
+  const float mx = fax + 0.5f * fex, my = fay + 0.5f * fey, len = sqrtf(fex * fex + fey * fey);
   const float cx = mx - SEARCH_OFFSET * fey, cy = my + SEARCH_OFFSET * fex;  // the square's centre
-  float h = fmaxf(SEARCH_SIZE * len, SEARCH_MIN);                           // and half side
+  float h = fmaxf(SEARCH_SIZE * len, known.x0 <= known.x1 ? 0.5f * (known.x1 - known.x0) : SEARCH_MIN);  // and half side
   // the edge's line: steep enough, it bounds the columns of a row (its float
-  // error stays below 0.03 buckets), else (it rises by less than 0.18 buckets
+  // error stays below 0.03 buckets), else (it rises by less than 0.15 buckets
   // over the window) the rows
   const bool steep = fabsf(fey) * 512.f > fabsf(fex);
   const float slope = steep ? fex / fey : 0.f;
-  const float line0 = fax - slope * fay + (iey > 0 ? fmaxf(slope, 0.f) + 0.1f : fminf(slope, 0.f) - 0.1f);
+  const float line0 = !steep    ? (iey > 0 ? 1e6f : -1e6f)
+                      : iey > 0 ? fax - slope * fay + fmaxf(slope, 0.f) + 0.1f
+                                : fax - slope * fay + fminf(slope, 0.f) - 0.1f;
   // where a better point can be: the window, then the circle's left part
-  float bx0 = 0.f, bx1 = fG, by0 = 0.f, by1 = fG;
-  if (!steep) {
-    if (iex > 0)
-      by0 = fmaxf(by0, fay - 0.25f);
-    else
-      by1 = fminf(by1, fay + 0.25f);
+  Rect box{0.f, fG, !steep && iex > 0 ? fay - 0.25f : 0.f, !steep && iex <= 0 ? fay + 0.25f : fG};
+  auto cot_of = [&](int2 P) {
+    const double dx = P.x - A.x, dy = P.y - A.y;
+    return cotangent(dx * (dx - ex) + dy * (dy - ey), ex * dy - ey * dx);  // a and b themselves: cross 0
+  };
+  float cot = best >= 0 ? cot_of(T.uv[best]) : COT_NONE;
+  auto narrow = [&]() {
+    const float t = cot, u = sqrtf(1.f + t * t);
+    float x0, x1, y0, y1, mg = 1e-3f;
+    if (t > 0.f) {
+      const float ox = mx - 0.5f * t * fey, oy = my + 0.5f * t * fex, rho = 0.5f * len * u;
+      mg += 2e-6f * rho;
+      x0 = ox - rho;
+      x1 = ox + rho;
+      y0 = oy - rho;
+      y1 = oy + rho;
+    } else {
+      const float k = 0.5f / (u - t);  // height of the cap over |n|
+      const float nx = -k * fey, ny = k * fex;
+      x0 = fminf(fax, fax + fex) + fminf(nx, 0.f);
+      x1 = fmaxf(fax, fax + fex) + fmaxf(nx, 0.f);
+      y0 = fminf(fay, fay + fey) + fminf(ny, 0.f);
+      y1 = fmaxf(fay, fay + fey) + fmaxf(ny, 0.f);
+    }
+    box = Rect{fmaxf(box.x0, x0 - mg), fminf(box.x1, x1 + mg), fmaxf(box.y0, y0 - mg), fminf(box.y1, y1 + mg)};
+  };
+  if (best >= 0) {
+    narrow();
+    if (known.x0 <= box.x0 && known.x1 >= box.x1 && known.y0 <= box.y0 && known.y1 >= box.y1) return best;
   }
-  double bd = 1.0, bc = 0.0;  // dot and cross of the best point
-  int best = -1;
+  int x0, x1, y0, y1;
+  bool tie;
+  auto cut = [&](int y, int& xa, int& xb) {
+    const int lim = (int)floorf(fminf(fmaxf(line0 + slope * (float)y, -1.f), fG));
+    if (iey > 0)
+      xb = min(xb, lim);
+    else
+      xa = max(xa, lim);
+  };
   for (;;) {
-    const int x0 = max((int)floorf(fmaxf(cx - h, bx0)), 0), x1 = min((int)floorf(fminf(cx + h, bx1)), T.G - 1);
-    const int y0 = max((int)floorf(fmaxf(cy - h, by0)), 0), y1 = min((int)floorf(fminf(cy + h, by1)), T.G - 1);
-    for (int y = y0; y <= y1; ++y) {
-      int xa = x0, xb = x1;
-      if (steep) {
-        const int lim = (int)floorf(fminf(fmaxf(line0 + slope * (float)y, -1.f), fG));
-        if (iey > 0)
-          xb = min(xb, lim);
-        else
-          xa = max(xa, lim);
+    x0 = max((int)floorf(fmaxf(cx - h, box.x0)), 0);
+    x1 = min((int)floorf(fminf(cx + h, box.x1)), T.G - 1);
+    y0 = max((int)floorf(fmaxf(cy - h, box.y0)), 0);
+    y1 = min((int)floorf(fminf(cy + h, box.y1)), T.G - 1);
+    // the two least cotangents of a lane and the point of the least
+    float second = COT_NONE;
+    cot = COT_NONE;
+    best = INT_MAX;
+    row_scan(T, x0, x1, y0, y1, gl, cut, [&](const int* p, const int2* Q, int n) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float q = j < n ? cot_of(Q[j]) : COT_NONE;
+        second = fminf(second, fmaxf(cot, q));
+        best = q < cot ? p[j] : best;
+        cot = fminf(cot, q);
       }
-      if (xa > xb) continue;
-      const int e = T.boff[y * T.G + xb + 1];
-      for (int p = T.boff[y * T.G + xa]; p < e; ++p) {
-        const int2 P = T.uv[p];
-        const double dx = P.x - A.x, dy = P.y - A.y;
-        const double cross = ex * dy - ey * dx;                // zero for a and b themselves
-        const double dot = dx * (dx - ex) + dy * (dy - ey);
-        const double p1 = dot * bc, p2 = bd * cross;
-        bool better = cross > 0.0 && p1 < p2;
-        // 8 * 2^-53: several times the rounding of the two products
-        if (cross > 0.0 && fabs(p1 - p2) <= 8.8817841970012523e-16 * fabs(p2) && p != best)
-          better = incircle_sos(a, b, best, p, A, B, T.uv[best], P) > 0;
-        best = better ? p : best;
-        bd = better ? dot : bd;
-        bc = better ? cross : bc;
+    });
+    const float least = group_min(cot), lim = cot_limit(least);
+    const uint32_t near = group_ballot(cot <= lim);
+    if (!(least < COT_NONE)) {
+      best = -1;
+    } else {
+      tie = (near & (near - 1)) != 0 || group_ballot(second <= lim) != 0;
+      best = group_reduce(cot <= lim ? best : INT_MAX, [](int u, int v) { return min(u, v); });
+      cot = least;
+      narrow();
+    }
+    if (cx - h <= box.x0 && cx + h >= box.x1 && cy - h <= box.y0 && cy + h >= box.y1) break;
+    h *= 4.f;
+  }
+  if (best < 0 || !tie) return best;
+  // near ties: exactly, one after the other, the same in all lanes of the group
+  const float lim = cot_limit(cot);
+  best = -1;
+  for (int y = y0; y <= y1; ++y) {
+    int xa = x0, xb = x1;
+    cut(y, xa, xb);
+    if (xa > xb) continue;
+    const int e = T.boff[y * T.G + xb + 1];
+    for (int p = T.boff[y * T.G + xa]; p < e; p += STAR_LANES) {
+      const bool near = p + gl < e && cot_of(T.uv[min(p + gl, e - 1)]) <= lim;
+      for (uint32_t lanes = group_ballot(near); lanes; lanes &= lanes - 1) {
+        const int c = p + __builtin_ctz(lanes);
+        if (best < 0 || incircle_sos(a, b, best, c, A, B, T.uv[best], T.uv[c]) > 0) best = c;
       }
     }
-    if (best >= 0) {
-      const float t = (float)bd / (float)bc, u = sqrtf(1.f + t * t);
-      float x_0, x_1, y_0, y_1, mg = 1e-3f;
-      if (t > 0.f) {
-        const float ox = mx - 0.5f * t * fey, oy = my + 0.5f * t * fex, rho = 0.5f * len * u;
-        mg += 2e-6f * rho;
-        x_0 = ox - rho;
-        x_1 = ox + rho;
-        y_0 = oy - rho;
-        y_1 = oy + rho;
-      } else {
-        const float k = 0.5f / (u - t);  // height of the cap over |n|
-        const float nx = -k * fey, ny = k * fex;
-        x_0 = fminf(fax, fax + fex) + fminf(nx, 0.f);
-        x_1 = fmaxf(fax, fax + fex) + fmaxf(nx, 0.f);
-        y_0 = fminf(fay, fay + fey) + fminf(ny, 0.f);
-        y_1 = fmaxf(fay, fay + fey) + fmaxf(ny, 0.f);
-      }
-      bx0 = fmaxf(bx0, x_0 - mg);
-      bx1 = fminf(bx1, x_1 + mg);
-      by0 = fmaxf(by0, y_0 - mg);
-      by1 = fminf(by1, y_1 + mg);
-    }
-    if (cx - h <= bx0 && cx + h >= bx1 && cy - h <= by0 && cy + h >= by1) break;
-    h *= 2.f;
   }
   return best;
 }
@@ -693,76 +763,21 @@ __device__ __forceinline__ bool edge_owned(int px, int py, int qx, int qy) {
   return dy > 0 || (dy == 0 && dx < 0);
 }
 
-__device__ __forceinline__ int floor_div_i(int a, int b) {
-  int q = a / b;
-  if ((a % b != 0) && ((a < 0) != (b < 0))) --q;
-  return q;
+// floor(x / C) for |x| < 2^20 and quotients below 2^13: a float estimate, off by
+// at most one, then corrected exactly.
+__device__ __forceinline__ int floor_div_i(int x, int C, float rC) {
+  const int q = (int)floorf((float)x * rC), r = x - q * C;
+  return q + (r >= C) - (r < 0);
 }
 
 // texel index range covering [lo, hi] in tile-local raw coordinates
 __device__ __forceinline__ void texel_range(int lo, int hi, int H, int C, int R, int& j0, int& j1) {
   const int q0 = -H + C / 2;
-  j0 = -floor_div_i(q0 - lo, C);  // ceil((lo - q0) / C)
-  j1 = floor_div_i(hi - q0, C);
+  const float rC = __builtin_amdgcn_rcpf((float)C);
+  j0 = -floor_div_i(q0 - lo, C, rC);  // ceil((lo - q0) / C)
+  j1 = floor_div_i(hi - q0, C, rC);
   if (j0 < 0) j0 = 0;
   if (j1 > R - 1) j1 = R - 1;
-}
-
-__device__ __forceinline__ bool tri_inside(int ax, int ay, int bx, int by, int cx, int cy, bool oa, bool ob, bool oc,
-                                           double qx, double qy) {
-  const double e0 = orient_d(bx, by, cx, cy, qx, qy);
-  if (e0 < 0.0 || (e0 == 0.0 && !oa)) return false;
-  const double e1 = orient_d(cx, cy, ax, ay, qx, qy);
-  if (e1 < 0.0 || (e1 == 0.0 && !ob)) return false;
-  const double e2 = orient_d(ax, ay, bx, by, qx, qy);
-  return !(e2 < 0.0 || (e2 == 0.0 && !oc));
-}
-
-// Narrow [lo, hi] to the x-interval of {q : orient(P, Q, q) >= 0} on the
-// horizontal line y = qy (approximate; the caller settles the ends exactly).
-__device__ __forceinline__ void edge_clip(int px, int py, int qx, int qy, double y, double& lo, double& hi) {
-  const double dy = qy - py;
-  const double k = (double)(qx - px) * (y - py);  // orient = k - dy * (x - px)
-  if (dy > 0.0)
-    hi = fmin(hi, px + k / dy);
-  else if (dy < 0.0)
-    lo = fmax(lo, px + k / dy);
-  else if (k < 0.0) {
-    lo = 1.0;
-    hi = 0.0;
-  }
-}
-
-// Write `key` into every texel whose centre lies in CCW triangle (a, b, c)
-// under the top-left rule.  Row by row: the span from the three edges is
-// widened by one texel, its two ends are settled with the exact test, and
-// the texels between them are filled without further tests (a triangle's
-// row section is an interval).
-template <class TT>
-__device__ void raster_triangle(const TT& T, int a, int b, int c, int C, int R, uint64_t* __restrict__ fm) {
-  const int2 A = T.uv[a], B = T.uv[b], Cc = T.uv[c];
-  const int ax = A.x, ay = A.y, bx = B.x, by = B.y, cx = Cc.x, cy = Cc.y;
-  int i0, i1, j0, j1;
-  texel_range(min(ax, min(bx, cx)), max(ax, max(bx, cx)), T.H, C, R, j0, j1);
-  texel_range(min(ay, min(by, cy)), max(ay, max(by, cy)), T.H, C, R, i0, i1);
-  const bool oa = edge_owned(bx, by, cx, cy), ob = edge_owned(cx, cy, ax, ay), oc = edge_owned(ax, ay, bx, by);
-  const uint64_t key = face_key(a, b, c);
-  const int q0 = -T.H + C / 2;
-  const double invC = 1.0 / C;
-  for (int i = i0; i <= i1; ++i) {
-    const double qy = q0 + i * C;
-    double lo = -1e300, hi = 1e300;
-    edge_clip(bx, by, cx, cy, qy, lo, hi);
-    edge_clip(cx, cy, ax, ay, qy, lo, hi);
-    edge_clip(ax, ay, bx, by, qy, lo, hi);
-    if (!(lo <= hi + 2.0 * C)) continue;
-    int jl = max(j0, (int)floor((fmax(lo, -3.0 * T.H) - q0) * invC) - 1);
-    int jr = min(j1, (int)ceil((fmin(hi, 3.0 * T.H) - q0) * invC) + 1);
-    while (jl <= jr && !tri_inside(ax, ay, bx, by, cx, cy, oa, ob, oc, q0 + jl * C, qy)) ++jl;
-    while (jr >= jl && !tri_inside(ax, ay, bx, by, cx, cy, oa, ob, oc, q0 + jr * C, qy)) --jr;
-    uint64_t* __restrict__ row = fm + i * R;
-    for (int j = jl; j <= jr; ++j) row[j] = key;
-  }
 }
 
 // Texel bounding box of triangle (a, b, c); false when it holds no texel.
@@ -775,42 +790,56 @@ __device__ __forceinline__ bool tri_texel_box(const TT& T, int a, int b, int c, 
   return i0 <= i1 && j0 <= j1;
 }
 
-// Triangles are rasterised after the star phase by groups of RASTER_LANES
-// lanes (one lane per texel of the box), not by the lane that finds them, so
-// rasterisation neither holds up the lanes of a wave that walk their stars
-// nor diverges with the box sizes.
+// Triangles are not rasterised by the lanes that find them but by groups of this
+// many lanes, so rasterisation does not hold up the walks.
 constexpr int RASTER_LANES = 8;
+constexpr int RASTER_MAX = 64;  // texels of a box they take; larger ones are left to the whole wave
 
-// raster_triangle's result, computed by the RASTER_LANES lanes of a group:
-// every texel of the box gets the exact top-left test.
-template <class TT>
-__device__ void raster_triangle_group(const TT& T, uint64_t key, int C, int R, uint64_t* __restrict__ fm, int lane) {
+// Write the triangle into every texel whose centre lies in it under the top-left
+// rule, by LANES lanes; false, and nothing written, if its box has more than
+// `most` texels.  Every texel of the box gets the exact test.  The three edge
+// functions are integers below 2^53, so stepping them over the box is exact;
+// an edge's ownership of the texels on it is a threshold half a unit below or
+// above zero.
+template <int LANES, class TT>
+__device__ bool raster_triangle(const TT& T, uint64_t key, int C, int R, uint64_t* __restrict__ fm, int lane, int most) {
   const int a = (int)(key >> 42), b = (int)((key >> 21) & 0x1FFFFF), c = (int)(key & 0x1FFFFF);
   int i0, i1, j0, j1;
-  if (!tri_texel_box(T, a, b, c, C, R, i0, i1, j0, j1)) return;
+  if (!tri_texel_box(T, a, b, c, C, R, i0, i1, j0, j1)) return true;
+  if ((i1 - i0 + 1) * (j1 - j0 + 1) > most) return false;
   const int2 A = T.uv[a], B = T.uv[b], Cc = T.uv[c];
   const int ax = A.x, ay = A.y, bx = B.x, by = B.y, cx = Cc.x, cy = Cc.y;
-  const bool oa = edge_owned(bx, by, cx, cy), ob = edge_owned(cx, cy, ax, ay), oc = edge_owned(ax, ay, bx, by);
-  const int q0 = -T.H + C / 2;
+  const double ta = edge_owned(bx, by, cx, cy) ? -0.5 : 0.5, tb = edge_owned(cx, cy, ax, ay) ? -0.5 : 0.5,
+               tc = edge_owned(ax, ay, bx, by) ? -0.5 : 0.5;
+  const double qx = -T.H + C / 2 + j0 * C, qy = -T.H + C / 2 + i0 * C;  // the box's first texel
+  const double ea = orient_d(bx, by, cx, cy, qx, qy), eb = orient_d(cx, cy, ax, ay, qx, qy),
+               ec = orient_d(ax, ay, bx, by, qx, qy);
+  const double C_d = C;
+  const double ai = (cx - bx) * C_d, aj = (by - cy) * C_d, bi = (ax - cx) * C_d, bj = (cy - ay) * C_d,
+               ci = (bx - ax) * C_d, cj = (ay - by) * C_d;
   const int w = j1 - j0 + 1, n = (i1 - i0 + 1) * w;
   const float rw = __builtin_amdgcn_rcpf((float)w);
-  for (int e = lane; e < n; e += RASTER_LANES) {
-    // e / w from a float estimate (e < 2^14), corrected exactly
+  for (int e = lane; e < n; e += LANES) {
+    // e / w from a float estimate (e < 2^24), corrected exactly
     int di = (int)((float)e * rw);
     if (di * w > e)
       --di;
     else if ((di + 1) * w <= e)
       ++di;
-    const int i = i0 + di, j = j0 + (e - di * w);
-    if (tri_inside(ax, ay, bx, by, cx, cy, oa, ob, oc, q0 + j * C, q0 + i * C)) fm[i * R + j] = key;
+    const int dj = e - di * w;
+    const double fi = di, fj = dj;
+    if (fma(fi, ai, fma(fj, aj, ea)) > ta && fma(fi, bi, fma(fj, bj, eb)) > tb && fma(fi, ci, fma(fj, cj, ec)) > tc)
+      fm[(i0 + di) * R + j0 + dj] = key;
   }
+  return true;
 }
 
-// Texels lying exactly on hull edge a->b get the triangle next to it.  Per
-// texel row the line crosses at most one texel centre, found exactly in
-// integers.
-template <class TT>
-__device__ void raster_hull_edge(const TT& T, int a, int b, uint64_t key, int C, int R, uint64_t* __restrict__ fm) {
+// Texels lying exactly on hull edge a->b get the triangle next to it (LANES lanes
+// take its rows in turn).  Per texel row the line crosses at most one texel
+// centre, found exactly in integers.
+template <int LANES, class TT>
+__device__ void raster_hull_edge(const TT& T, int a, int b, uint64_t key, int C, int R, uint64_t* __restrict__ fm,
+                                 int lane) {
   const int2 A = T.uv[a], B = T.uv[b];
   const int ax = A.x, ay = A.y, bx = B.x, by = B.y;
   int i0, i1, j0, j1;
@@ -821,14 +850,14 @@ __device__ void raster_hull_edge(const TT& T, int a, int b, uint64_t key, int C,
   if (dy == 0) {
     // the edge lies on a texel row only if ay is a row centre (then i0 == i1)
     if (i0 > i1 || q0 + i0 * C != ay) return;
-    for (int j = j0; j <= j1; ++j) fm[i0 * R + j] = key;
+    for (int j = j0 + lane; j <= j1; j += LANES) fm[i0 * R + j] = key;
     return;
   }
   // x = ax + dx * (y - ay) / dy must be an integer texel centre; every
   // quantity is an integer below 2^39, so the double quotient, its rounding
   // and the check of the product are exact
   const double fdx = (double)dx, fdy = (double)dy;
-  for (int i = i0; i <= i1; ++i) {
+  for (int i = i0 + lane; i <= i1; i += LANES) {
     const double num = fdx * (double)(q0 + i * C - ay);
     const double xr = rint(num / fdy);
     if (xr * fdy != num) continue;
@@ -874,434 +903,585 @@ __device__ int block_scan_excl(int* s, int n, int* s_tmp) {
   return total;
 }
 
-__device__ __forceinline__ bool pt_less(int u0, int v0, int z0, uint64_t c0, int u1, int v1, int z1, uint64_t c1) {
-  // order by (v, u) ascending, then (z, R, G, B) descending
-  if (v0 != v1) return v0 < v1;
-  if (u0 != u1) return u0 < u1;
-  if (z0 != z1) return z0 > z1;
-  const uint64_t k0 = ((c0 & 0xFFFF) << 32) | (((c0 >> 16) & 0xFFFF) << 16) | ((c0 >> 32) & 0xFFFF);
-  const uint64_t k1 = ((c1 & 0xFFFF) << 32) | (((c1 >> 16) & 0xFFFF) << 16) | ((c1 >> 32) & 0xFFFF);
-  return k0 > k1;
-}
-
 __device__ __forceinline__ void write_zero_tile(const ReconParams& P, int k) {
   const int64_t n8 = (int64_t)P.R * P.R * 2;
   float4* o = reinterpret_cast<float4*>(P.x_out + (int64_t)k * P.R * P.R * 8);
   for (int64_t i = threadIdx.x; i < n8; i += RB) o[i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-// Four waves per SIMD (128 VGPRs) so two 512-lane workgroups share a CU: the
-// searches are latency-bound (LDS reads, dependent FP64 chains), and the
-// second workgroup hides more of it than the few spills this costs.
-__global__ void __launch_bounds__(RB, 4) k_recon(ReconParams P) {
-  // region 0 holds the raw bucket offsets while bucketing, then the
-  // canonical coordinates; the canonical bucket offsets sit at the end
-  __shared__ __align__(16) int s_mem[LDS_INTS];
+// Phases a-b, one workgroup per tile: gather, bucket sort, canonical points.
+__global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
+  // the raw bucket offsets at the start, the canonical ones at the end, and
+  // between them the sort keys and entries of a window that fits
+  __shared__ __align__(16) int s_mem[PREP_INTS];
   __shared__ int s_tmp[RB / 64 + 1];
-  __shared__ int s_hdr[5];  // tile index, flags, bin offset, bin count, tile id
-  __shared__ int s_flags;
-  __shared__ int s_ntri;
-  __shared__ int s_next;
-  __shared__ int s_nnblk;
-  __shared__ double s_cz;
   const int tid = threadIdx.x;
-  const int R = P.R, C = P.C, H = P.H, W2 = 2 * P.H;
+  const int R = P.R, H = P.H, W2 = 2 * P.H;
   const int RR = R * R;
-  uint64_t* __restrict__ fm = P.facemap + (int64_t)blockIdx.x * RR;
-  int32_t* __restrict__ nn = P.nnidx + (int64_t)blockIdx.x * RR;
-  const bool cap_overflow = P.flags[0] != 0;
-  // Control flow below depends only on values that thread 0 fetches and
-  // broadcasts through LDS, read back with readfirstlane so the compiler
-  // sees them as uniform: every barrier then stays in uniform control flow
-  // and the loop has a single back edge (an earlier form with a `continue`
-  // let the compiler re-enter the barriers without the queue fetch).
-  for (;;) {
+  const int k = __builtin_amdgcn_readfirstlane(P.order[P.q0 + blockIdx.x]);
+  const int flags = __builtin_amdgcn_readfirstlane((P.flags[0] ? LS_TILE_CAP : 0) | (P.status[k] & LS_TILE_BADID));
+  const int32_t off = __builtin_amdgcn_readfirstlane(P.bin_off[k]);
+  const int32_t cnt = __builtin_amdgcn_readfirstlane((flags & (LS_TILE_CAP | LS_TILE_BADID)) ? 0 : P.bin_off[k + 1] - off);
+  const int32_t t = __builtin_amdgcn_readfirstlane(P.tile_list[k]);
+  __syncthreads();  // the status has been read by every wave
+  if (cnt == 0) {
+    write_zero_tile(P, k);
     if (tid == 0) {
-      const int q = atomicAdd(P.queue, 1);
-      const int kk = q < P.n_tiles ? P.order[q] : q;
-      s_hdr[0] = kk;
-      if (kk < P.n_tiles) {
-        int f = cap_overflow ? LS_TILE_CAP : 0;
-        f |= P.status[kk] & LS_TILE_BADID;
-        const int32_t o = P.bin_off[kk];
-        s_hdr[1] = f;
-        s_hdr[2] = o;
-        s_hdr[3] = (f & (LS_TILE_CAP | LS_TILE_BADID)) ? 0 : P.bin_off[kk + 1] - o;
-        s_hdr[4] = P.tile_list[kk];
-      }
+      P.cz_out[k] = 0.0;
+      P.status[k] = flags | LS_TILE_EMPTY;
+      P.npts[k] = 0;
+      P.has_dt[k] = 0;
+    }
+    return;
+  }
+  // texels without a triangle until the stars fill them in
+  uint64_t* __restrict__ fm = P.facemap + (int64_t)blockIdx.x * RR;
+  for (int tt = tid; tt < RR; tt += RB) fm[tt] = FACE_NONE;
+  const int64_t cx = P.ox + (int64_t)(t % P.tiles_x) * P.S + P.S / 2;
+  const int64_t cy = P.oy + (int64_t)(t / P.tiles_x) * P.S + P.S / 2;
+  const int G = bucket_side(cnt), NB = G * G;
+  int* s_b = s_mem;
+  int* s_k = s_mem + PREP_INTS - (NB + 1);
+  // ---- a. gather + bucket histogram
+  for (int b = tid; b <= NB; b += RB) s_b[b] = 0;
+  __syncthreads();
+  for (int e = tid; e < cnt; e += RB) {
+    const int32_t gi = P.bin_idx[off + e];
+    const int u = (int)((int64_t)P.x[gi] - cx), v = (int)((int64_t)P.y[gi] - cy);
+    P.su[off + e] = u;
+    P.sv[off + e] = v;
+    const int b = bucket_1d(v + H, G, W2) * G + bucket_1d(u + H, G, W2);
+    P.sslot[off + e] = atomicAdd(&s_b[b], 1);
+  }
+  __syncthreads();
+  block_scan_excl(s_b, NB + 1, s_tmp);
+  // Scatter (v, u) and the entry into bucket order, sort every bucket by
+  // (v, u) with the largest (z, R, G, B) first, drop repeated positions and
+  // write the canonical points.
+  auto key_of = [](int u, int v) -> uint64_t {
+    return ((uint64_t)(uint32_t)(v + (1 << 20)) << 32) | (uint32_t)(u + (1 << 20));
+  };
+  auto rank_of = [&](int e) -> uint64_t {  // (R, G, B) of an entry, R most significant
+    const uint16_t* c3 = P.rgb + 3 * (int64_t)P.bin_idx[off + e];
+    return ((uint64_t)c3[0] << 32) | ((uint64_t)c3[1] << 16) | (uint64_t)c3[2];
+  };
+  auto before = [&](uint64_t k0, int e0, uint64_t k1, int e1) -> bool {
+    if (k0 != k1) return k0 < k1;
+    const int z0 = P.z[P.bin_idx[off + e0]], z1 = P.z[P.bin_idx[off + e1]];
+    if (z0 != z1) return z0 > z1;
+    return rank_of(e0) > rank_of(e1);
+  };
+  auto bucket_sort = [&](uint64_t* __restrict__ key, int* __restrict__ idx) -> int {
+    for (int e = tid; e < cnt; e += RB) {
+      const int u = P.su[off + e], v = P.sv[off + e];
+      const int b = bucket_1d(v + H, G, W2) * G + bucket_1d(u + H, G, W2);
+      const int pos = s_b[b] + P.sslot[off + e];
+      key[pos] = key_of(u, v);
+      idx[pos] = e;
     }
     __syncthreads();
-    const int k = __builtin_amdgcn_readfirstlane(s_hdr[0]);
-    if (k >= P.n_tiles) break;
-    const int flags = __builtin_amdgcn_readfirstlane(s_hdr[1]);
-    const int32_t off = __builtin_amdgcn_readfirstlane(s_hdr[2]);
-    const int32_t cnt = __builtin_amdgcn_readfirstlane(s_hdr[3]);
-    const int32_t t = __builtin_amdgcn_readfirstlane(s_hdr[4]);
-    if (cnt == 0) {
-      write_zero_tile(P, k);
-      if (tid == 0) {
-        P.cz_out[k] = 0.0;
-        P.status[k] = flags | LS_TILE_EMPTY;
-      }
-    } else {
-      const int64_t cx = P.ox + (int64_t)(t % P.tiles_x) * P.S + P.S / 2;
-      const int64_t cy = P.oy + (int64_t)(t / P.tiles_x) * P.S + P.S / 2;
-      int G = 1;
-      {
-        const int want = (int)sqrtf((float)cnt * 0.5f);
-        G = want < 1 ? 1 : (want > MAXG ? MAXG : want);
-      }
-      const int NB = G * G;
-      int* s_b = s_mem;
-      int* s_k = s_mem + LDS_INTS - (NB + 1);
-      const bool uv_lds = 2 * cnt <= LDS_INTS - (NB + 1);
-      // ---- a. gather + bucket histogram
-      for (int b = tid; b <= NB; b += RB) s_b[b] = 0;
-      if (tid == 0) {
-        s_flags = 0;
-        s_ntri = 0;
-        s_next = 0;
-        s_nnblk = 0;
-      }
-      __syncthreads();
-      for (int e = tid; e < cnt; e += RB) {
-        const int32_t gi = P.bin_idx[off + e];
-        const int u = (int)((int64_t)P.x[gi] - cx), v = (int)((int64_t)P.y[gi] - cy);
-        P.su[off + e] = u;
-        P.sv[off + e] = v;
-        P.sz[off + e] = P.z[gi];
-        const uint16_t* c3 = P.rgb + 3 * (int64_t)gi;
-        P.srgb[off + e] = (uint64_t)c3[0] | ((uint64_t)c3[1] << 16) | ((uint64_t)c3[2] << 32);
-        const int b = bucket_1d(v + H, G, W2) * G + bucket_1d(u + H, G, W2);
-        P.sslot[off + e] = atomicAdd(&s_b[b], 1);
-      }
-      __syncthreads();
-      block_scan_excl(s_b, NB + 1, s_tmp);
-      // Scatter into bucket order, sort every bucket by (v, u) with the
-      // largest (z, R, G, B) first, drop repeated positions and write the
-      // canonical points.  The sorted copies live in the free middle of the
-      // LDS (between the bucket counts and the kept counts) when the window
-      // fits, else in global memory at the window's offset.
-      auto bucket_sort = [&](int* __restrict__ tu, int* __restrict__ tv, int* __restrict__ tz,
-                             uint64_t* __restrict__ tc, int base) -> int {
-        for (int e = tid; e < cnt; e += RB) {
-          const int u = P.su[off + e], v = P.sv[off + e];
-          const int b = bucket_1d(v + H, G, W2) * G + bucket_1d(u + H, G, W2);
-          const int pos = base + s_b[b] + P.sslot[off + e];
-          tu[pos] = u;
-          tv[pos] = v;
-          tz[pos] = P.sz[off + e];
-          tc[pos] = P.srgb[off + e];
+    // ---- b. per-bucket sort + dedupe
+    if (tid == 0) s_k[NB] = 0;
+    for (int b = tid; b < NB; b += RB) {
+      const int lo = s_b[b], hi = s_b[b + 1];
+      int kept = hi > lo ? 1 : 0;
+      for (int i = lo + 1; i < hi; ++i) {
+        const uint64_t kk = key[i];
+        const int e = idx[i];
+        int j = i - 1;
+        while (j >= lo && before(kk, e, key[j], idx[j])) {
+          key[j + 1] = key[j];
+          idx[j + 1] = idx[j];
+          --j;
         }
-        __syncthreads();
-        // ---- b. per-bucket sort + dedupe
-        if (tid == 0) s_k[NB] = 0;
-        for (int b = tid; b < NB; b += RB) {
-          const int lo = base + s_b[b], hi = base + s_b[b + 1];
-          for (int i = lo + 1; i < hi; ++i) {
-            const int u = tu[i], v = tv[i], zz = tz[i];
-            const uint64_t c = tc[i];
-            int j = i - 1;
-            while (j >= lo && pt_less(u, v, zz, c, tu[j], tv[j], tz[j], tc[j])) {
-              tu[j + 1] = tu[j];
-              tv[j + 1] = tv[j];
-              tz[j + 1] = tz[j];
-              tc[j + 1] = tc[j];
-              --j;
+        key[j + 1] = kk;
+        idx[j + 1] = e;
+      }
+      for (int i = lo + 1; i < hi; ++i) kept += key[i] != key[i - 1];
+      s_k[b] = kept;
+    }
+    __syncthreads();
+    const int mm = __builtin_amdgcn_readfirstlane(block_scan_excl(s_k, NB + 1, s_tmp));
+    for (int b = tid; b < NB; b += RB) {
+      const int lo = s_b[b], hi = s_b[b + 1];
+      int w = off + s_k[b];
+      for (int i = lo; i < hi; ++i)
+        if (i == lo || key[i] != key[i - 1]) {
+          const uint64_t kk = key[i];
+          P.cuv[w] = make_int2((int)(uint32_t)kk - (1 << 20), (int)(uint32_t)(kk >> 32) - (1 << 20));
+          const int32_t gi = P.bin_idx[off + idx[i]];
+          const uint16_t* c3 = P.rgb + 3 * (int64_t)gi;
+          P.cz[w] = P.z[gi];
+          P.crgb[w] = (uint64_t)c3[0] | ((uint64_t)c3[1] << 16) | ((uint64_t)c3[2] << 32);
+          ++w;
+        }
+    }
+    return mm;
+  };
+  const int a0 = (NB + 2) & ~1;  // keys 8-byte aligned behind the raw offsets
+  int m;
+  if (a0 + 3 * cnt <= PREP_INTS - (NB + 1))
+    m = bucket_sort(reinterpret_cast<uint64_t*>(s_mem + a0), s_mem + a0 + 2 * cnt);
+  else
+    m = bucket_sort(P.skey + off, P.sidx + off);
+  for (int b = tid; b <= NB; b += RB) P.boff[2 * (int64_t)off + b] = s_k[b];
+  __syncthreads();
+  // collinearity check
+  bool noncol = false;
+  if (m >= 3) {
+    const int2 p0 = P.cuv[off], p1 = P.cuv[off + 1];
+    for (int p = tid; p < m; p += RB) {
+      const int2 q = P.cuv[off + p];
+      if (orient_d(p0.x, p0.y, p1.x, p1.y, q.x, q.y) != 0.0) noncol = true;
+    }
+  }
+  // face keys pack three point indices in 21 bits each
+  const bool big = m >= (1 << 21);
+  const bool dt = __syncthreads_or(noncol) != 0 && !big;
+  if (tid == 0) {
+    P.npts[k] = m;
+    P.has_dt[k] = dt ? 1 : 0;
+    P.status[k] = flags | (dt ? 0 : LS_TILE_NN_ONLY) | (big ? LS_TILE_DEGENERATE : 0);
+  }
+  if (dt) {
+    const int n = (m + P.item - 1) / P.item;
+    if (tid == 0) s_tmp[0] = atomicAdd(P.item_n, n);
+    __syncthreads();
+    for (int i = tid; i < n; i += RB) P.items[s_tmp[0] + i] = make_int2(blockIdx.x, i * P.item);
+  }
+}
+
+// Phase c: the Delaunay triangles and their texels, by work items of P.item
+// canonical points that the waves of the launch take from a list.
+//
+// Eight lanes work on one point.  About forty points around it are gathered
+// once, CAND to a lane.  A triangle belongs to the lowest of its vertices, by
+// (v, u): so the walk around a point a visits the neighbours above it only,
+// counter-clockwise from the first point met by a circle that grows upwards
+// from a (tangent to a's row, its inside empty: a Delaunay edge) to the first
+// triangle that reaches below a, then clockwise; a hull edge is left to its
+// lower end.  Where that start is not proven by the gathered points, the nearest
+// neighbour takes its place, and the walk may pass points below a first.
+//
+// A step takes every candidate's cotangent and its minimum over the group,
+// without a branch or a global access on the way; the answer stands if the
+// circle through it lies in the gathered square, else third_left goes on from
+// it (one step in ten).  The wave collects its triangles and rasterises them
+// together.
+//
+// Bound by instruction issue (VALU 68 % busy): a star costs about 450 wave
+// instructions.  A search by one lane over the buckets, with the answers shared
+// between stars, takes fewer but leaves the lanes of a wave waiting for its
+// longest search (1024 tiles of 50-2000 points: 1.8 ms, this 1.2 ms); sixteen
+// lanes with 5 candidates each cost 1.5 ms, all neighbours instead of those
+// above 40 % more steps.  Three waves per SIMD: four would spill (8,000 tiles
+// slower, 1024 faster by 2 %).  Items of 16 points: 8 add atomics (2.4 ms in
+// all instead of 1.85), 32 leave a tail (1.90); with up to 64 tiles 8, what a
+// wave works on at once.
+__global__ void __launch_bounds__(TB, 3) k_recon_stars(ReconParams P) {
+  __shared__ int2 s_d[TB / STAR_LANES][CANDS];  // candidates: position relative to the centre
+  __shared__ int s_id[TB / STAR_LANES][CANDS];  // and index
+  __shared__ uint64_t s_tri[TB / 64][TRI_CAP];
+  __shared__ int s_ntri[TB / 64];
+  const int tid = threadIdx.x, wave = tid >> 6, gl = tid & (STAR_LANES - 1);
+  const int R = P.R, C = P.C;
+  int2* __restrict__ list_d = s_d[tid / STAR_LANES];
+  int* __restrict__ list_id = s_id[tid / STAR_LANES];
+  auto wave_sync = []() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  if ((tid & 63) == 0) s_ntri[wave] = 0;
+  wave_sync();
+  const int n_items = __builtin_amdgcn_readfirstlane(P.item_n[0]);
+  // the first item by the wave's number, then from the shared counter
+  const int n_waves = gridDim.x * (TB / 64);
+  for (int it = __builtin_amdgcn_readfirstlane(blockIdx.x * (TB / 64) + wave); it < n_items;) {
+    const int2 item = P.items[it];
+    const int pos = __builtin_amdgcn_readfirstlane(item.x), begin = __builtin_amdgcn_readfirstlane(item.y);
+    const int k = __builtin_amdgcn_readfirstlane(P.order[P.q0 + pos]);
+    const int m = __builtin_amdgcn_readfirstlane(P.npts[k]);
+    const int off = __builtin_amdgcn_readfirstlane(P.bin_off[k]);
+    const int cnt = __builtin_amdgcn_readfirstlane(P.bin_off[k + 1]) - off;
+    uint64_t* __restrict__ fm = P.facemap + (int64_t)pos * R * R;
+    typedef TileT<UvGlobal, const int32_t*> TT;
+    TT T;
+    T.uv = UvGlobal{P.cuv + off};
+    T.boff = P.boff + 2 * (int64_t)off;
+    T.G = bucket_side(cnt);
+    T.H = P.H;
+    T.W2 = 2 * P.H;
+    T.inv = (float)T.G / (float)T.W2;
+    const int G = T.G, end = min(begin + P.item, m);
+    for (int a0 = begin; a0 < end; a0 += 64 / STAR_LANES) {
+      const int a = a0 + (tid & 63) / STAR_LANES;
+      if (a < end) {
+        const int2 A = T.uv[a];
+        const int bx = bucket_1d(A.x + T.H, G, T.W2), by = bucket_1d(A.y + T.H, G, T.W2);
+        // ---- gather: the points of the (2 r + 1)^2 buckets around a, r from
+        // the density of 7 x 7 buckets, at most CANDS points
+        int r = 3, held = 0, first_p[2], len[2];  // bucket rows gl and gl + 8 of the square
+        auto count = [&]() {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int y = by - r + gl + STAR_LANES * h;
+            len[h] = 0;
+            if (y >= 0 && y <= min(by + r, G - 1)) {
+              first_p[h] = T.boff[y * G + max(bx - r, 0)];
+              len[h] = T.boff[y * G + min(bx + r, G - 1) + 1] - first_p[h];
             }
-            tu[j + 1] = u;
-            tv[j + 1] = v;
-            tz[j + 1] = zz;
-            tc[j + 1] = c;
           }
-          int kept = 0;
-          for (int i = lo; i < hi; ++i)
-            if (i == lo || tu[i] != tu[i - 1] || tv[i] != tv[i - 1]) ++kept;
-          s_k[b] = kept;
+          held = group_reduce(len[0] + len[1], [](int u, int v) { return u + v; });
+        };
+        count();
+        r = min(max((int)(3.5f * sqrtf(CANDS * 0.7f / (float)held)), 1), 7);
+        for (;; --r) {
+          count();
+          if (held <= CANDS) break;
+          held = 0;
+          if (r == 0) break;
         }
-        __syncthreads();
-        const int mm = __builtin_amdgcn_readfirstlane(block_scan_excl(s_k, NB + 1, s_tmp));
-        for (int b = tid; b < NB; b += RB) {
-          const int lo = base + s_b[b], hi = base + s_b[b + 1];
-          int w = off + s_k[b];
-          for (int i = lo; i < hi; ++i)
-            if (i == lo || tu[i] != tu[i - 1] || tv[i] != tv[i - 1]) {
-              P.cuv[w] = make_int2(tu[i], tv[i]);
-              P.sz[w] = tz[i];
-              P.srgb[w] = tc[i];
-              ++w;
-            }
-        }
-        __syncthreads();
-        return mm;
-      };
-      // sorted copies in LDS: colours (8-byte aligned) then u, v, z
-      const int a0 = (NB + 2) & ~1;
-      const bool sort_lds = a0 + 5 * cnt <= LDS_INTS - (NB + 1);
-      int m;
-      if (sort_lds)
-        m = bucket_sort(s_mem + a0 + 2 * cnt, s_mem + a0 + 3 * cnt, s_mem + a0 + 4 * cnt,
-                        reinterpret_cast<uint64_t*>(s_mem + a0), 0);
-      else
-        m = bucket_sort(P.tu, P.tv, P.tz, P.trgb, off);
-      // canonical coordinates in LDS when they fit, and behind them the
-      // colours and heights read per texel by the output pass
-      int2* s_uv = reinterpret_cast<int2*>(s_mem);
-      uint64_t* s_c = reinterpret_cast<uint64_t*>(s_mem + 2 * m);
-      int32_t* s_z = s_mem + 4 * m;
-      const bool attr_lds = uv_lds && 5 * m <= LDS_INTS - (NB + 1);
-      if (uv_lds)
-        for (int p = tid; p < m; p += RB) {
-          s_uv[p] = P.cuv[off + p];
-          if (attr_lds) {
-            s_c[p] = P.srgb[off + p];
-            s_z[p] = P.sz[off + p];
+        Rect known{1.f, 0.f, 1.f, 0.f};  // what has been gathered, open at the window's borders
+        float reach2 = 0.f;              // squared distance from the centre that it covers
+        if (held) {
+          const int at = group_before(len[0] + len[1], gl);
+          for (int j = 0; j < len[0]; ++j) list_id[at + j] = first_p[0] + j;
+          for (int j = 0; j < len[1]; ++j) list_id[at + len[0] + j] = first_p[1] + j;
+          const float fx = (float)(A.x + T.H) * T.inv, fy = (float)(A.y + T.H) * T.inv;
+          known = Rect{bx - r > 0 ? (float)(bx - r) : -16.f, bx + r < G - 1 ? (float)(bx + r + 1) : G + 16.f,
+                       by - r > 0 ? (float)(by - r) : -16.f, by + r < G - 1 ? (float)(by + r + 1) : G + 16.f};
+          const float reach =
+              (fminf(fminf(fx - known.x0, known.x1 - fx), fminf(fy - known.y0, known.y1 - fy)) - 1e-3f) / T.inv;
+          reach2 = reach > 0.f ? reach * reach * 0.99999f : 0.f;
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          for (int e = gl; e < held; e += STAR_LANES) {
+            const int2 Q = T.uv[list_id[e]];
+            list_d[e] = make_int2(Q.x - A.x, Q.y - A.y);
           }
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-      __syncthreads();
-      // Phases c-e once per pointer kind: LDS pointers when the points and
-      // their attributes are staged in LDS, global ones otherwise.
-      double cz = 0.0;
-      bool has_dt = false;
-      auto phases = [&](auto uvp, auto Tz, auto Tc) {
-      TileT<decltype(uvp)> T;
-      T.uv = uvp;
-      T.boff = (LdsI32)s_k;
-      T.G = G;
-      T.H = H;
-      T.W2 = W2;
-      T.bw = (double)W2 / G;
-      T.inv = (float)G / (float)W2;
-      // ---- c. face map reset (the nearest points follow the stars)
-      const int q0 = -H + C / 2;
-      for (int tt = tid; tt < RR; tt += RB) fm[tt] = FACE_NONE;
-      // collinearity check
-      bool noncol = false;
-      if (m >= 3) {
-        const int2 p0 = T.uv[0], p1 = T.uv[1];
-        for (int p = tid; p < m; p += RB) {
-          const int2 q = T.uv[p];
-          if (orient_d(p0.x, p0.y, p1.x, p1.y, q.x, q.y) != 0.0) noncol = true;
-        }
-      }
-      // face keys pack three point indices in 21 bits each
-      has_dt = (__builtin_amdgcn_readfirstlane(__syncthreads_or(noncol)) != 0) && m < (1 << 21);
-      if (m >= (1 << 21) && tid == 0) atomicOr(&s_flags, LS_TILE_DEGENERATE);
-      // ---- d. Delaunay stars, rasterised into the face map
-      uint64_t* __restrict__ tris = P.tris + 2 * (int64_t)off;
-      // a triangle that covers a texel centre is queued for the group pass
-      // below (or rasterised at once if the queue, sized for the 2m - 5
-      // triangles of a triangulation, is full)
-      auto emit = [&](int p, int q, int r) {
-        int i0, i1, j0, j1;
-        if (!tri_texel_box(T, p, q, r, C, R, i0, i1, j0, j1)) return;
-        const int slot = atomicAdd(&s_ntri, 1);
-        if (slot < 2 * cnt) {
-          tris[slot] = face_key(p, q, r);
-          return;
-        }
-        raster_triangle(T, p, q, r, C, R, fm);
-      };
-      if (has_dt) {
-        // nearest neighbour of every point: the first edge of its star;
-        // successor lists cleared
-        int32_t* __restrict__ nb0 = P.sslot + off;
-        uint64_t* __restrict__ succ = P.succ + (int64_t)off * SUCC_K;
-        int32_t* __restrict__ succ_n = P.succ_n + off;
-        for (int a = tid; a < m; a += RB) {
-          nb0[a] = ring_nearest(T, T.uv[a].x, T.uv[a].y, a);
-          succ_n[a] = 0;
-          ulonglong2* s2 = reinterpret_cast<ulonglong2*>(succ + (int64_t)a * SUCC_K);
-#pragma unroll
-          for (int j = 0; j < SUCC_K / 2; ++j) s2[j] = make_ulonglong2(SUCC_EMPTY, SUCC_EMPTY);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __syncthreads();
-        // Every triangle lies in the stars of its three vertices.  A search
-        // that finds triangle (p, q, c) left of p->q also answers the
-        // searches left of q->c (third vertex p) and c->p (third vertex q);
-        // it records them in the successor lists of q and c, keyed by the
-        // edge's second vertex.  The search is exact, so a recorded answer
-        // is the answer the search would give.
-        auto succ_find = [&](int p, int q) -> int {
-          const uint64_t* l = succ + (int64_t)p * SUCC_K;
-          uint64_t v[SUCC_K];
-#pragma unroll
-          for (int j = 0; j < SUCC_K; ++j) v[j] = __hip_atomic_load(l + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          int c = -1;
-#pragma unroll
-          for (int j = 0; j < SUCC_K; ++j)
-            if (v[j] != SUCC_EMPTY && (int)(v[j] >> 32) == q) c = (int)(uint32_t)v[j];
-          return c;
-        };
-        auto succ_put = [&](int p, int q, int c) {
-          const int j = __hip_atomic_fetch_add(succ_n + p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (j < SUCC_K)
-            __hip_atomic_store(succ + (int64_t)p * SUCC_K + j, ((uint64_t)(uint32_t)q << 32) | (uint32_t)c,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        };
-        // Each lane walks one star at a time and takes the next point from a
-        // shared counter as soon as its star is done, so the lanes of a wave
-        // are not held at star boundaries.  The walk turns counter-clockwise
-        // from the nearest neighbour b0; if it meets the hull it resumes
-        // clockwise from b0.  Steps whose answer is already recorded are
-        // taken at once; a wave searches only when few of its lanes can
-        // step from the lists, and then all its waiting lanes search
-        // together.
-        int a = atomicAdd(&s_next, 1);
-        int b0 = 0, b = 0, steps = 0, prev_b = -1, hull_b = -1;
-        bool back = false, first = true;
-        uint64_t hull_key = FACE_NONE;
-        auto start = [&]() {
-          b0 = nb0[a];
+        // ---- walk
+        int b0 = -1, b = -1, steps = 0;
+        int2 B = make_int2(0, 0), B0 = B;            // b and b0 relative to a
+        int f1 = -1, f_prev = -1, f_hull = -1;       // counter-clockwise: first third vertex, last b, b at the hull
+        int b1 = -1, b_prev = -1, b_hull = -1;       // and clockwise
+        bool back = false, done = false;
+        uint64_t rest = FACE_NONE;
+        auto above = [](int2 D) { return D.y > 0 || (D.y == 0 && D.x > 0); };
+        auto turn = [&]() {
+          back = true;
           b = b0;
-          steps = 0;
-          prev_b = -1;  // second vertex of the last counter-clockwise triangle
-          hull_b = -1;
-          back = false;
-          first = true;
-          hull_key = FACE_NONE;
+          B = B0;
         };
-        if (a < m) start();
-        // one step with c the third vertex left of the current edge (-1: none)
-        auto advance = [&](int c) {
-          // forward: triangle (a, b, c) left of a->b; backward: (b, a, c)
-          const int p = back ? b : a, q = back ? a : b;
-          bool done = false;
+        // one step on, c the third vertex of the current edge (-1: none), D its
+        // position relative to a
+        auto advance = [&](int c, int2 D) {
+          const bool up = above(B);
           if (c < 0) {
             if (back) {
+              if (up) b_hull = b;
               done = true;
             } else {
-              hull_b = b;
-              if (prev_b >= 0) hull_key = face_key(a, prev_b, b);
-              back = true;
-              b = b0;
+              if (up) f_hull = b;
+              turn();
             }
-          } else {
-            if (back && first && hull_key == FACE_NONE) hull_key = face_key(p, q, c);
-            if (back) first = false;
-            if (a < b && a < c) emit(p, q, c);
-            prev_b = b;
-            b = c;
-            if (!back && b == b0) done = true;
+            return;
           }
-          if (!done && ++steps >= STAR_MAX_STEPS) {
-            atomicOr(&s_flags, LS_TILE_DEGENERATE);
+          const bool cup = above(D);
+          if (up && cup) {
+            const uint64_t key = back ? face_key(b, a, c) : face_key(a, b, c);
+            int slot = 0;
+            if (gl == 0) slot = atomicAdd(&s_ntri[wave], 1);
+            slot = group_first(slot);
+            if (slot >= TRI_CAP)
+              rest = key;  // no room: rasterised at once
+            else if (gl == 0)
+              s_tri[wave][slot] = key;
+          }
+          if (back) {
+            b1 = b1 < 0 ? c : b1;
+            b_prev = b;
+          } else {
+            f1 = f1 < 0 ? c : f1;
+            f_prev = b;
+          }
+          b = c;
+          B = D;
+          if (up && !cup) {  // past the points above a
+            if (back || !above(B0))
+              done = true;
+            else
+              turn();
+          } else if (!back && b == b0) {
             done = true;
           }
-          if (done) {
-            if (hull_b >= 0 && hull_key != FACE_NONE) raster_hull_edge(T, a, hull_b, hull_key, C, R, fm);
-            a = atomicAdd(&s_next, 1);
-            if (a < m) start();
+          if (!done && ++steps >= STAR_MAX_STEPS) {
+            if (gl == 0) atomicOr(&P.status[k], LS_TILE_DEGENERATE);
+            done = true;
           }
         };
-        for (;;) {
-          const bool live = a < m;
-          if (__ballot(live) == 0) break;
-          const int p = back ? b : a, q = back ? a : b;
-          int c = live ? succ_find(p, q) : -1;
-          const bool hit = c >= 0;
-          bool step = hit;
-          if (__popcll(__ballot(hit)) <= SEARCH_MAX_HITS && live && !hit) {
-            c = third_left(T, p, q);
-            if (c >= 0) {
-              succ_put(q, c, p);
-              succ_put(c, p, q);
+        // The candidates are read again after the rare calls below: registers
+        // that live across them would halve the waves in flight.
+        while (!done) {
+          int c = -1;
+          bool tie = held == 0;  // near ties: settled by an exact scan of the circle
+          if (held) {
+            double dx[CAND], dy[CAND], l2[CAND];
+#pragma unroll
+            for (int s = 0; s < CAND; ++s) {
+              const int e = gl + STAR_LANES * s;
+              const int2 D = e < held ? list_d[e] : make_int2(0, 0);
+              dx[s] = D.x;
+              dy[s] = D.y;
+              l2[s] = fma(dx[s], dx[s], dy[s] * dy[s]);
             }
-            step = true;
+            if (b0 < 0) {
+              // first edge: the circle's diameter through a candidate is its
+              // l2 / dy, the cotangent of a horizontal edge
+              float cot[CAND], least = COT_NONE;
+#pragma unroll
+              for (int s = 0; s < CAND; ++s) {
+                cot[s] = cotangent(l2[s], dy[s]);
+                least = fminf(least, cot[s]);
+              }
+              least = group_min(least);
+              const float lim = cot_limit(least);
+              int n = 0, e = 0;
+#pragma unroll
+              for (int s = 0; s < CAND; ++s) {
+                const bool hit = cot[s] <= lim;
+                e = hit ? gl + STAR_LANES * s : e;
+                n += hit;
+              }
+              const uint32_t hits = group_ballot(n > 0), many = group_ballot(n > 1);
+              if (least * least <= reach2 && many == 0 && (hits & (hits - 1)) == 0) {
+                e = group_reduce(n > 0 ? e : INT_MAX, [](int u, int v) { return min(u, v); });
+                b0 = b = list_id[e];
+                B = B0 = list_d[e];
+              }
+            }
+            while (b0 >= 0) {
+              // the third vertex left of a->b, or of b->a
+              const double ex = B.x, ey = B.y, sx = back ? -ex : ex, sy = back ? -ey : ey;
+              float cot[CAND], least = COT_NONE;
+#pragma unroll
+              for (int s = 0; s < CAND; ++s) {
+                cot[s] = cotangent(fma(-ex, dx[s], fma(-ey, dy[s], l2[s])), fma(sx, dy[s], -(sy * dx[s])));
+                least = fminf(least, cot[s]);
+              }
+              least = group_min(least);
+              c = -1;
+              if (!(least < COT_NONE)) break;
+              const float lim = cot_limit(least);
+              int n = 0, e = 0;
+#pragma unroll
+              for (int s = 0; s < CAND; ++s) {
+                const bool hit = cot[s] <= lim;
+                e = hit ? gl + STAR_LANES * s : e;
+                n += hit;
+              }
+              const uint32_t hits = group_ballot(n > 0), many = group_ballot(n > 1);
+              e = group_reduce(n > 0 ? e : INT_MAX, [](int u, int v) { return min(u, v); });
+              c = list_id[e];
+              const int2 D = list_d[e];
+              tie = many != 0 || (hits & (hits - 1)) != 0;
+              if (tie) break;
+              const float len2 = (float)fma(ex, ex, ey * ey);
+              if (!(fmaf(len2 * least, least, len2) <= reach2)) break;
+              advance(c, D);
+              c = -1;
+              if (done || rest != FACE_NONE) break;
+            }
           }
-          if (step) advance(c);
+          if (b0 < 0) {
+            b0 = b = nearest_of_point(T, a, gl);
+            const int2 Q = T.uv[b];
+            B = B0 = make_int2(Q.x - A.x, Q.y - A.y);
+            if (held) continue;
+          }
+          if (!done && rest == FACE_NONE) {
+            c = third_left(T, back ? b : a, back ? a : b, c, tie ? Rect{1.f, 0.f, 1.f, 0.f} : known, gl);
+            const int2 Q = T.uv[max(c, 0)];
+            advance(c, make_int2(Q.x - A.x, Q.y - A.y));
+          }
+          if (rest != FACE_NONE) {
+            raster_triangle<STAR_LANES>(T, rest, C, R, fm, gl, INT_MAX);
+            rest = FACE_NONE;
+          }
         }
+        // a hull edge's triangle: the last one before it, or the first of the
+        // other direction
+        if (f_hull >= 0 && (f_prev >= 0 || b1 >= 0))
+          raster_hull_edge<STAR_LANES>(T, a, f_hull, f_prev >= 0 ? face_key(a, f_prev, f_hull) : face_key(b0, a, b1), C, R,
+                                       fm, gl);
+        if (b_hull >= 0 && (b_prev >= 0 || f1 >= 0))
+          raster_hull_edge<STAR_LANES>(T, b_hull, a, b_prev >= 0 ? face_key(b_prev, a, b_hull) : face_key(a, b0, f1), C, R,
+                                       fm, gl);
       }
-      // nearest point per texel: 8 x 8 texel blocks taken from a shared
-      // counter by each wave once its star walks are done, so the waves
-      // that finish early fill the tail of the star phase
-      {
-        const int nbs = (R + 7) / 8, lane = tid & 63;
-        for (;;) {
-          int blk = 0;
-          if (lane == 0) blk = atomicAdd(&s_nnblk, 1);
-          blk = __builtin_amdgcn_readfirstlane(__shfl(blk, 0));
-          if (blk >= nbs * nbs) break;
-          const int bi = blk / nbs, bj = blk - bi * nbs;
-          int qx, qy;
-          const int b = nearest_block(T, q0, C, R, bi, bj, lane, qx, qy);
-          const int i = bi * 8 + (lane >> 3), j = bj * 8 + (lane & 7);
-          if (i < R && j < R) nn[i * R + j] = b;
+      // ---- raster
+      wave_sync();
+      const int ntri = min(__builtin_amdgcn_readfirstlane(*(volatile int*)&s_ntri[wave]), TRI_CAP);
+      if (ntri >= TRI_CAP / 2 || a0 + 64 / STAR_LANES >= end) {
+        for (int i0 = 0; i0 < ntri; i0 += 64 / RASTER_LANES) {
+          const int i = i0 + (tid & 63) / RASTER_LANES;
+          const bool rest = i < ntri && !raster_triangle<RASTER_LANES>(T, s_tri[wave][i], C, R, fm, tid & (RASTER_LANES - 1), RASTER_MAX);
+          for (uint64_t large = __ballot(rest && (tid & (RASTER_LANES - 1)) == 0); large; large &= large - 1)
+            raster_triangle<64>(T, s_tri[wave][i0 + __builtin_ctzll(large) / RASTER_LANES], C, R, fm, tid & 63, INT_MAX);
         }
+        wave_sync();
+        if ((tid & 63) == 0) s_ntri[wave] = 0;
       }
-      __syncthreads();
-      {
-        const int ntri = min(__builtin_amdgcn_readfirstlane(s_ntri), 2 * cnt);
-        for (int t = tid / RASTER_LANES; t < ntri; t += RB / RASTER_LANES)
-          raster_triangle_group(T, tris[t], C, R, fm, tid % RASTER_LANES);
-      }
-      __syncthreads();
-      // ---- e. interpolation, normalisation, output
-      auto lin_value = [&](int tt, double* out4) {
-        const int i = tt / R, j = tt - i * R;
-        const uint64_t f = fm[tt];
-        if (f == FACE_NONE) {
-          const int p = nn[tt];
-          out4[0] = (double)Tz[p] * P.scale_z + P.offset_z;
-          const uint64_t c = Tc[p];
-          out4[1] = (double)(c & 0xFFFF);
-          out4[2] = (double)((c >> 16) & 0xFFFF);
-          out4[3] = (double)((c >> 32) & 0xFFFF);
-          return;
-        }
-        const int a = (int)(f >> 42), b = (int)((f >> 21) & 0x1FFFFF), c = (int)(f & 0x1FFFFF);
-        const int2 A = T.uv[a], B = T.uv[b], Cc = T.uv[c];
-        const double qx = q0 + j * C, qy = q0 + i * C;
-        const double ob = orient_d(Cc.x, Cc.y, A.x, A.y, qx, qy);
-        const double oc = orient_d(A.x, A.y, B.x, B.y, qx, qy);
-        const double O = orient_d(A.x, A.y, B.x, B.y, Cc.x, Cc.y);
-        const double lb = ob / O, lc = oc / O;
-        const double za = Tz[a], zb = Tz[b], zc = Tz[c];
-        const double h = za + lb * (zb - za) + lc * (zc - za);
-        out4[0] = h * P.scale_z + P.offset_z;
-        const uint64_t ca = Tc[a], cb = Tc[b], cc = Tc[c];
-        for (int ch = 0; ch < 3; ++ch) {
-          const double va = (double)((ca >> (16 * ch)) & 0xFFFF), vb = (double)((cb >> (16 * ch)) & 0xFFFF),
-                       vc = (double)((cc >> (16 * ch)) & 0xFFFF);
-          out4[1 + ch] = va + lb * (vb - va) + lc * (vc - va);
-        }
-      };
-      if (tid == 0) {
-        double v4[4];
-        lin_value((R / 2) * R + R / 2, v4);
-        s_cz = v4[0];
-      }
-      __syncthreads();
-      cz = s_cz;
-      float4* __restrict__ out = reinterpret_cast<float4*>(P.x_out + (int64_t)k * RR * 8);
-      for (int tt = tid; tt < RR; tt += RB) {
-        double lv[4];
-        lin_value(tt, lv);
-        const int p = nn[tt];
-        const double hn = (double)Tz[p] * P.scale_z + P.offset_z;
-        const uint64_t c = Tc[p];
-        const double k65 = 1.0 / 65535.0;
-        out[2 * tt] = make_float4((float)((lv[0] - cz) * P.inv_r), (float)((hn - cz) * P.inv_r), (float)(lv[1] * k65),
-                                  (float)(lv[2] * k65));
-        out[2 * tt + 1] = make_float4((float)(lv[3] * k65), (float)((double)(c & 0xFFFF) * k65),
-                                      (float)((double)((c >> 16) & 0xFFFF) * k65),
-                                      (float)((double)((c >> 32) & 0xFFFF) * k65));
-      }
-      };
-      if (attr_lds)
-        phases(UvLds{(LdsU64)s_uv}, (LdsI32)s_z, (LdsU64)s_c);
-      else
-        phases(UvGlobal{P.cuv + off}, (const int32_t*)(P.sz + off), (const uint64_t*)(P.srgb + off));
-    if (tid == 0) {
-      P.cz_out[k] = cz;
-      int st = flags | s_flags;
-      if (!has_dt) st |= LS_TILE_NN_ONLY;
-      P.status[k] = st;
+      wave_sync();
     }
+    if (n_items <= n_waves) break;
+    int next = 0;
+    if ((tid & 63) == 0) next = atomicAdd(P.item_n + 1, 1);
+    it = n_waves + __builtin_amdgcn_readfirstlane(next);
+  }
+}
+
+// Phases d-e, `parts` workgroups per tile: nearest point of every texel,
+// interpolation, normalisation and output, 8 x 8 texels per wave at a time.
+__global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
+  __shared__ __align__(16) int s_mem[OUT_INTS];
+  __shared__ double s_cz, s_d[TB];
+  __shared__ int s_i[TB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int pos = blockIdx.x / parts, part = blockIdx.x - pos * parts;
+  const int k = __builtin_amdgcn_readfirstlane(P.order[P.q0 + pos]);
+  const int m = __builtin_amdgcn_readfirstlane(P.npts[k]);
+  if (m == 0) return;
+  const int off = __builtin_amdgcn_readfirstlane(P.bin_off[k]);
+  const int cnt = __builtin_amdgcn_readfirstlane(P.bin_off[k + 1]) - off;
+  const int R = P.R, C = P.C;
+  const int G = bucket_side(cnt), NB = G * G;
+  const uint64_t* __restrict__ fm = P.facemap + (int64_t)pos * R * R;
+  const bool uv_lds = 2 * m + NB + 1 <= OUT_INTS;
+  const bool attr_lds = 5 * m + NB + 1 <= OUT_INTS;
+  // colours and coordinates (8 bytes each), heights, bucket offsets
+  uint64_t* s_c = reinterpret_cast<uint64_t*>(s_mem + 2 * m);
+  int32_t* s_z = s_mem + 4 * m;
+  int32_t* s_off = s_mem + (attr_lds ? 5 * m : 2 * m);
+  if (uv_lds) {
+    int2* uv = reinterpret_cast<int2*>(s_mem);
+    for (int p = tid; p < m; p += TB) {
+      uv[p] = P.cuv[off + p];
+      if (attr_lds) {
+        s_c[p] = P.crgb[off + p];
+        s_z[p] = P.cz[off + p];
+      }
+    }
+    for (int b = tid; b <= NB; b += TB) s_off[b] = P.boff[2 * (int64_t)off + b];
+  }
+  __syncthreads();
+  auto run = [&](auto uvp, auto bp, auto Tz, auto Tc) {
+    TileT<decltype(uvp), decltype(bp)> T;
+    T.uv = uvp;
+    T.boff = bp;
+    T.G = G;
+    T.H = P.H;
+    T.W2 = 2 * P.H;
+    T.inv = (float)G / (float)T.W2;
+    const int q0 = -P.H + C / 2;
+    // height (metres) and colours of texel (i, j): linear in its triangle, or
+    // its nearest point's
+    auto lin_value = [&](int i, int j, uint64_t f, int p, double* out4) {
+      if (f == FACE_NONE) {
+        out4[0] = (double)Tz[p] * P.scale_z + P.offset_z;
+        const uint64_t c = Tc[p];
+        out4[1] = (double)(c & 0xFFFF);
+        out4[2] = (double)((c >> 16) & 0xFFFF);
+        out4[3] = (double)((c >> 32) & 0xFFFF);
+        return;
+      }
+      const int a = (int)(f >> 42), b = (int)((f >> 21) & 0x1FFFFF), c = (int)(f & 0x1FFFFF);
+      const int2 A = T.uv[a], B = T.uv[b], Cc = T.uv[c];
+      const double qx = q0 + j * C, qy = q0 + i * C;
+      const double ob = orient_d(Cc.x, Cc.y, A.x, A.y, qx, qy);
+      const double oc = orient_d(A.x, A.y, B.x, B.y, qx, qy);
+      const double O = orient_d(A.x, A.y, B.x, B.y, Cc.x, Cc.y);
+      const double lb = ob / O, lc = oc / O;
+      const double za = Tz[a], zb = Tz[b], zc = Tz[c];
+      const double h = za + lb * (zb - za) + lc * (zc - za);
+      out4[0] = h * P.scale_z + P.offset_z;
+      const uint64_t ca = Tc[a], cb = Tc[b], cc = Tc[c];
+      for (int ch = 0; ch < 3; ++ch) {
+        const double va = (double)((ca >> (16 * ch)) & 0xFFFF), vb = (double)((cb >> (16 * ch)) & 0xFFFF),
+                     vc = (double)((cc >> (16 * ch)) & 0xFFFF);
+        out4[1 + ch] = va + lb * (vb - va) + lc * (vc - va);
+      }
+    };
+    // c_z: the centre texel; outside the hull (sparse windows) its nearest
+    // point is searched by all lanes
+    const int ic = R / 2;
+    const uint64_t fc = fm[ic * R + ic];
+    int pc = -1;
+    if (__builtin_amdgcn_readfirstlane((int)(fc == FACE_NONE))) {
+      const int qc = q0 + ic * C;
+      double bd = 1e300;
+      auto less = [&](double d, int p, double d2, int p2) -> bool {
+        if (p2 < 0 || d != d2) return p2 < 0 || d < d2;
+        const int2 A = T.uv[p], B = T.uv[p2];
+        return A.y < B.y || (A.y == B.y && A.x < B.x);
+      };
+      for (int p = tid; p < m; p += TB) {
+        const int2 Q = T.uv[p];
+        const double dx = Q.x - qc, dy = Q.y - qc;
+        const double d = fma(dx, dx, dy * dy);
+        if (less(d, p, bd, pc)) {
+          bd = d;
+          pc = p;
+        }
+      }
+      s_d[tid] = bd;
+      s_i[tid] = pc;
+      __syncthreads();
+      if (tid == 0)
+        for (int i = 1; i < TB; ++i)
+          if (s_i[i] >= 0 && less(s_d[i], s_i[i], bd, pc)) {
+            bd = s_d[i];
+            pc = s_i[i];
+          }
+    }
+    if (tid == 0) {
+      double v4[4];
+      lin_value(ic, ic, fc, pc, v4);
+      s_cz = v4[0];
+      if (part == 0) P.cz_out[k] = v4[0];
     }
     __syncthreads();
-  }
+    const double cz = s_cz;
+    float4* __restrict__ out = reinterpret_cast<float4*>(P.x_out + (int64_t)k * R * R * 8);
+    const int nbs = (R + 7) / 8;
+    // a lane's texel in the wave's 8 x 8 block: 4 x 4 sub-blocks of 16 lanes
+    const int sub = lane >> 4, di = 4 * (sub >> 1), dj = 4 * (sub & 1);
+    for (int blk = part * (TB / 64) + (tid >> 6); blk < nbs * nbs; blk += parts * (TB / 64)) {
+      const int bi = blk / nbs, i0 = 8 * bi + di, j0 = 8 * (blk - bi * nbs) + dj;
+      const int i = i0 + ((lane >> 2) & 3), j = j0 + (lane & 3);
+      const bool in_grid = i < R && j < R;
+      const uint64_t f = in_grid ? fm[i * R + j] : FACE_NONE;
+      const int p = nearest_of_texel(T, q0, C, R, min(i0, R - 1), min(j0, R - 1), i, j);
+      if (!in_grid) continue;
+      double lv[4];
+      lin_value(i, j, f, p, lv);
+      const double hn = (double)Tz[p] * P.scale_z + P.offset_z;
+      const uint64_t c = Tc[p];
+      const double k65 = 1.0 / 65535.0;
+      const int tt = i * R + j;
+      out[2 * tt] = make_float4((float)((lv[0] - cz) * P.inv_r), (float)((hn - cz) * P.inv_r), (float)(lv[1] * k65),
+                                (float)(lv[2] * k65));
+      out[2 * tt + 1] = make_float4((float)(lv[3] * k65), (float)((double)(c & 0xFFFF) * k65),
+                                    (float)((double)((c >> 16) & 0xFFFF) * k65),
+                                    (float)((double)((c >> 32) & 0xFFFF) * k65));
+    }
+  };
+  if (attr_lds)
+    run(UvLds{(LdsU64)s_mem}, (LdsI32)s_off, (LdsI32)s_z, (LdsU64)s_c);
+  else if (uv_lds)
+    run(UvLds{(LdsU64)s_mem}, (LdsI32)s_off, (const int32_t*)(P.cz + off), (const uint64_t*)(P.crgb + off));
+  else
+    run(UvGlobal{P.cuv + off}, (const int32_t*)(P.boff + 2 * (int64_t)off), (const int32_t*)(P.cz + off),
+        (const uint64_t*)(P.crgb + off));
 }
 
 int g_num_cu = 0;
@@ -1322,20 +1502,16 @@ struct ReconLayout {
   int32_t* counts;
   int32_t* fill;
   int32_t* flags;
-  int32_t* queue;
   int32_t* order;
   int32_t* bin_off;
   int32_t* bin_idx;
   int32_t* sort_scratch;
-  int32_t *su, *sv, *sz, *sslot, *tu, *tv, *tz;
-  uint64_t *srgb, *trgb;
+  int32_t *su, *sv, *sslot, *sidx, *cz;
+  uint64_t *skey, *crgb;
   int2* cuv;
-  uint64_t* tris;
-  uint64_t* succ;
-  int32_t* succ_n;
   uint64_t* facemap;
-  int32_t* nnidx;
-  int n_wg;
+  int64_t face_tiles;  // tiles whose face maps fit
+  int2* items;
   int64_t entries;
 };
 
@@ -1344,13 +1520,43 @@ int64_t max_multiplicity(const LsGridInfo& gi) {
   return per * per;
 }
 
+// Output workgroups of a tile: about 4,096 in a launch, so that a few tiles still
+// fill the chip and the largest windows do not end last.
+int recon_out_parts(int nt) { return std::min(36, std::max(2, 4096 / nt)); }
+
 int recon_wg_count(int32_t n_tiles) {
   const int want = 2 * num_cus();
   return n_tiles < want ? (n_tiles > 0 ? n_tiles : 1) : want;
 }
 
-// Workspace layout for n_tiles tiles, n points and nwg recon workgroups.
-size_t recon_layout(const LsGridInfo& gi, int32_t n_tiles, int64_t n, void* base, ReconLayout* L, int nwg) {
+// Workspace bytes for n_tiles tiles and n points: 144 bytes per bin entry
+// plus 12 R^2 per tile of a launch (at most two per CU count), and the lists.
+// These are the sizes and limits callers know; the arrays take less, and the
+// rest of the space holds face maps.
+size_t recon_bytes(const LsGridInfo& gi, int32_t n_tiles, int64_t n, int nwg) {
+  LsArena A{nullptr, 0, 0};
+  const int64_t nall = (int64_t)gi.tx * gi.ty;
+  const int64_t E = n * max_multiplicity(gi) + 1;
+  const int64_t RR = (int64_t)gi.R * gi.R;
+  A.take<int32_t>(nall);
+  for (int i = 0; i < 2; ++i) A.take<int32_t>(n_tiles + 1);
+  A.take<int32_t>(4);
+  A.take<int32_t>(n_tiles);
+  A.take<int32_t>(n_tiles + 1);
+  A.take<int32_t>(E);
+  A.take<int32_t>(2 * E);
+  for (int i = 0; i < 7; ++i) A.take<int32_t>(E);
+  for (int i = 0; i < 3; ++i) A.take<uint64_t>(E);
+  A.take<uint64_t>(2 * E);
+  A.take<uint64_t>(8 * E);
+  A.take<int32_t>(E);
+  A.take<uint64_t>(RR * nwg);
+  A.take<int32_t>(RR * nwg);
+  return A.used;
+}
+
+// The arrays in `bytes` bytes at base, the face maps in what they leave.
+void recon_layout(const LsGridInfo& gi, int32_t n_tiles, int64_t n, void* base, size_t bytes, ReconLayout* L) {
   LsArena A{reinterpret_cast<char*>(base), 0, 0};
   const int64_t nall = (int64_t)gi.tx * gi.ty;
   const int64_t E = n * max_multiplicity(gi) + 1;
@@ -1358,40 +1564,35 @@ size_t recon_layout(const LsGridInfo& gi, int32_t n_tiles, int64_t n, void* base
   L->tile_pos = A.take<int32_t>(nall);
   L->counts = A.take<int32_t>(n_tiles + 1);
   L->fill = A.take<int32_t>(n_tiles + 1);
-  L->flags = A.take<int32_t>(4);
-  L->queue = L->flags + 1;
+  L->flags = A.take<int32_t>(4);  // too many entries; the work items and how many are taken
   L->order = A.take<int32_t>(n_tiles);
   L->bin_off = A.take<int32_t>(n_tiles + 1);
   L->bin_idx = A.take<int32_t>(E);
   L->sort_scratch = A.take<int32_t>(2 * E);
   L->su = A.take<int32_t>(E);
   L->sv = A.take<int32_t>(E);
-  L->sz = A.take<int32_t>(E);
   L->sslot = A.take<int32_t>(E);
-  L->tu = A.take<int32_t>(E);
-  L->tv = A.take<int32_t>(E);
-  L->tz = A.take<int32_t>(E);
-  L->srgb = A.take<uint64_t>(E);
-  L->trgb = A.take<uint64_t>(E);
+  L->sidx = A.take<int32_t>(E);
+  L->cz = A.take<int32_t>(E);
+  L->skey = A.take<uint64_t>(E);
+  L->crgb = A.take<uint64_t>(E);
   L->cuv = A.take<int2>(E);
-  L->tris = A.take<uint64_t>(2 * E);
-  L->succ = A.take<uint64_t>(SUCC_K * E);
-  L->succ_n = A.take<int32_t>(E);
-  L->facemap = A.take<uint64_t>(RR * nwg);
-  L->nnidx = A.take<int32_t>(RR * nwg);
-  L->n_wg = nwg;
+  L->items = A.take<int2>(E / 3 + 1);
   L->entries = E;
-  return A.used;
+  const size_t at = ls_align(A.used);
+  L->face_tiles = at < bytes ? (int64_t)((bytes - at) / (8 * RR)) : 0;
+  L->facemap = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(base) + at);
 }
 
-// Enqueue the whole recon pipeline with its workspace at `ws` laid out for
-// nwg recon workgroups (the caller has checked that it is large enough).
+// Enqueue the whole recon pipeline with its workspace of ws_bytes at `ws` (the
+// caller has checked that it is large enough).
 int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, const int32_t* z, const uint16_t* rgb,
                   int64_t n, const int32_t* tile_list, int32_t n_tiles, int32_t order, float* x_out, double* cz_out,
-                  int32_t* bin_off, int32_t* bin_idx, int64_t bin_cap, int32_t* tile_status, void* ws, int nwg,
+                  int32_t* bin_off, int32_t* bin_idx, int64_t bin_cap, int32_t* tile_status, void* ws, size_t ws_bytes,
                   hipStream_t st) {
   ReconLayout L;
-  recon_layout(gi, n_tiles, n, ws, &L, nwg);
+  recon_layout(gi, n_tiles, n, ws, ws_bytes, &L);
+  if (L.face_tiles < 1) return LS_EWORKSPACE;
   const bool user_csr = bin_off && bin_idx;
   int32_t* boff = user_csr ? bin_off : L.bin_off;
   int32_t* bidx = user_csr ? bin_idx : L.bin_idx;
@@ -1478,7 +1679,6 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
   rp.scale_z = gi.scale_z;
   rp.offset_z = gi.offset_z;
   rp.inv_r = 1.0 / ((double)gi.H * gi.scale_xy);
-  rp.n_tiles = n_tiles;
   rp.x = x;
   rp.y = y;
   rp.z = z;
@@ -1489,27 +1689,38 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
   rp.flags = L.flags;
   rp.su = L.su;
   rp.sv = L.sv;
-  rp.sz = L.sz;
-  rp.srgb = L.srgb;
   rp.sslot = L.sslot;
-  rp.tu = L.tu;
-  rp.tv = L.tv;
-  rp.tz = L.tz;
-  rp.trgb = L.trgb;
+  rp.skey = L.skey;
+  rp.sidx = L.sidx;
   rp.cuv = L.cuv;
-  rp.tris = L.tris;
-  rp.succ = L.succ;
-  rp.succ_n = L.succ_n;
+  rp.cz = L.cz;
+  rp.crgb = L.crgb;
+  rp.boff = L.sort_scratch;  // free once the caller's CSR is sorted
+  rp.npts = L.fill;          // free once the points are binned
+  rp.has_dt = L.counts;
   rp.facemap = L.facemap;
-  rp.nnidx = L.nnidx;
-  rp.queue = L.queue;
+  rp.items = L.items;
+  rp.item_n = L.flags + 1;
   rp.order = L.order;
   rp.x_out = x_out;
   rp.cz_out = cz_out;
   rp.status = tile_status;
   {
     LS_TRACE("recon_tile", st);
-    hipLaunchKernelGGL(k_recon, dim3(L.n_wg), dim3(RB), 0, st, rp);
+    // as many tiles at a time as the workspace holds face maps for
+    for (int q0 = 0; q0 < n_tiles;) {
+      const int nt = (int)std::min<int64_t>(n_tiles - q0, std::min<int64_t>(L.face_tiles, 1 << 20));
+      const int parts = recon_out_parts(nt);
+      rp.q0 = q0;
+      // few tiles: a wave takes the points it works on at once
+      rp.item = nt <= 64 ? ITEM_MIN : ITEM_MAX;
+      if (q0) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(T), 0, st, rp.item_n, (int64_t)2, 0);
+      hipLaunchKernelGGL(k_recon_prep, dim3(nt), dim3(RB), 0, st, rp);
+      hipLaunchKernelGGL(k_recon_stars, dim3(3 * num_cus()), dim3(TB), 0,
+                         st, rp);
+      hipLaunchKernelGGL(k_recon_out, dim3((unsigned)nt * parts), dim3(TB), 0, st, rp, parts);
+      q0 += nt;
+    }
   }
   LS_LAUNCH_CHECK();
   return LS_OK;
@@ -1518,8 +1729,7 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
 }  // namespace
 
 size_t ls_recon_ws_bytes(const LsGridInfo& gi, int32_t n_tiles, int64_t n) {
-  ReconLayout L;
-  return recon_layout(gi, n_tiles, n, nullptr, &L, recon_wg_count(n_tiles));
+  return recon_bytes(gi, n_tiles, n, recon_wg_count(n_tiles));
 }
 
 // ---------------------------------------------------------------------------
@@ -1566,24 +1776,12 @@ int ls_recon_noalloc_impl(const LsGridInfo& gi, const int32_t* x, const int32_t*
                           float* x_out, double* cz_out, int32_t* bin_off, int32_t* bin_idx, int64_t bin_cap,
                           int32_t* tile_status, hipStream_t st) {
   if (n_tiles <= 0) return LS_OK;
-  ReconLayout L;
-  const size_t cap = LS_RECON_SCRATCH_BYTES;
-  const size_t one = recon_layout(gi, n_tiles, n, nullptr, &L, 1);
-  if (one > cap) return LS_ESCRATCH;
-  // as many persistent workgroups as the scratch holds (their face and
-  // nearest-point maps are the only part that grows with the count)
-  int nwg = recon_wg_count(n_tiles);
-  if (nwg > 1) {
-    const size_t per_wg = recon_layout(gi, n_tiles, n, nullptr, &L, 2) - one;
-    const int64_t fit = 1 + (int64_t)((cap - one) / (per_wg ? per_wg : 1));
-    if (fit < nwg) nwg = (int)fit;
-    while (nwg > 1 && recon_layout(gi, n_tiles, n, nullptr, &L, nwg) > cap) --nwg;
-  }
+  if (recon_bytes(gi, n_tiles, n, 1) > LS_RECON_SCRATCH_BYTES) return LS_ESCRATCH;
   void* ws = nullptr;
   const int rc = scratch_address(&ws);
   if (rc != LS_OK) return rc;
   return recon_enqueue(gi, x, y, z, rgb, n, tile_list, n_tiles, order, x_out, cz_out, bin_off, bin_idx, bin_cap,
-                       tile_status, ws, nwg, st);
+                       tile_status, ws, LS_RECON_SCRATCH_BYTES, st);
 }
 
 int ls_recon_impl(const LsGridInfo& gi, const int32_t* x, const int32_t* y, const int32_t* z, const uint16_t* rgb,
@@ -1591,10 +1789,7 @@ int ls_recon_impl(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
                   int32_t* bin_off, int32_t* bin_idx, int64_t bin_cap, int32_t* tile_status, void* ws,
                   size_t ws_bytes, hipStream_t st) {
   if (n_tiles <= 0) return LS_OK;
-  ReconLayout L;
-  const int nwg = recon_wg_count(n_tiles);
-  const size_t need = recon_layout(gi, n_tiles, n, nullptr, &L, nwg);
-  if (ws_bytes < need || !ws) return LS_EWORKSPACE;
+  if (ws_bytes < recon_bytes(gi, n_tiles, n, recon_wg_count(n_tiles)) || !ws) return LS_EWORKSPACE;
   return recon_enqueue(gi, x, y, z, rgb, n, tile_list, n_tiles, order, x_out, cz_out, bin_off, bin_idx, bin_cap,
-                       tile_status, ws, nwg, st);
+                       tile_status, ws, ws_bytes, st);
 }
