@@ -119,6 +119,21 @@ __global__ void k_fill_i32(int32_t* __restrict__ a, int64_t n, int32_t v) {
     a[i] = v;
 }
 
+// Start values of the per-tile arrays, in one launch (five fills took 20 us of
+// gaps between launches).
+__global__ void k_recon_init(int32_t* __restrict__ tile_pos, int64_t n_all, int32_t* __restrict__ counts,
+                             int32_t* __restrict__ fill, int32_t* __restrict__ status, int32_t n_tiles,
+                             int32_t* __restrict__ flags) {
+  const int64_t step = (int64_t)gridDim.x * blockDim.x, first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  for (int64_t i = first; i < n_all; i += step) tile_pos[i] = 0x7fffffff;
+  for (int64_t i = first; i <= n_tiles; i += step) {
+    counts[i] = 0;
+    fill[i] = 0;
+    if (i < n_tiles) status[i] = 0;
+  }
+  if (first < 4) flags[first] = 0;
+}
+
 __global__ void k_tile_pos(const int32_t* __restrict__ tile_list, int32_t n_tiles, int64_t n_all,
                            int32_t* __restrict__ tile_pos, int32_t* __restrict__ status) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
@@ -132,16 +147,15 @@ __global__ void k_tile_pos(const int32_t* __restrict__ tile_list, int32_t n_tile
   atomicMin(&tile_pos[t], k);
 }
 
-__global__ void k_tile_dup(const int32_t* __restrict__ tile_list, int32_t n_tiles, int64_t n_all,
-                           const int32_t* __restrict__ tile_pos, int32_t* __restrict__ status) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n_tiles) return;
-  const int32_t t = tile_list[k];
-  if (t >= 0 && t < n_all && tile_pos[t] != k) status[k] = LS_TILE_BADID;
-}
-
-__global__ void k_tile_pos_fix(int32_t* __restrict__ tile_pos, int64_t n_all) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_all; i += (int64_t)gridDim.x * blockDim.x)
+// Listed tiles that lost their entry are flagged; entries nobody took become -1.
+__global__ void k_tile_pos_fix(const int32_t* __restrict__ tile_list, int32_t n_tiles, int64_t n_all,
+                               int32_t* __restrict__ tile_pos, int32_t* __restrict__ status) {
+  const int64_t step = (int64_t)gridDim.x * blockDim.x, first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  for (int64_t k = first; k < n_tiles; k += step) {
+    const int32_t t = tile_list[k];
+    if (t >= 0 && t < n_all && tile_pos[t] != k) status[k] = LS_TILE_BADID;
+  }
+  for (int64_t i = first; i < n_all; i += step)
     if (tile_pos[i] == 0x7fffffff) tile_pos[i] = -1;
 }
 
@@ -1602,16 +1616,13 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
   const int T = 256;
   LS_TRACE("recon_all", st);
   auto blocks = [&](int64_t cnt) { return (int)std::min<int64_t>((cnt + T - 1) / T, 65535); };
-  hipLaunchKernelGGL(k_fill_i32, dim3(blocks(nall)), dim3(T), 0, st, L.tile_pos, nall, 0x7fffffff);
-  hipLaunchKernelGGL(k_fill_i32, dim3(blocks(n_tiles + 1)), dim3(T), 0, st, L.counts, (int64_t)n_tiles + 1, 0);
-  hipLaunchKernelGGL(k_fill_i32, dim3(blocks(n_tiles + 1)), dim3(T), 0, st, L.fill, (int64_t)n_tiles + 1, 0);
-  hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(T), 0, st, L.flags, (int64_t)4, 0);
-  hipLaunchKernelGGL(k_fill_i32, dim3(blocks(n_tiles)), dim3(T), 0, st, tile_status, (int64_t)n_tiles, 0);
+  const int64_t most = std::max<int64_t>(nall, (int64_t)n_tiles + 1);
+  hipLaunchKernelGGL(k_recon_init, dim3(blocks(most)), dim3(T), 0, st, L.tile_pos, nall, L.counts, L.fill, tile_status,
+                     n_tiles, L.flags);
   hipLaunchKernelGGL(k_tile_pos, dim3(blocks(n_tiles)), dim3(T), 0, st, tile_list, n_tiles, nall, L.tile_pos,
                      tile_status);
-  hipLaunchKernelGGL(k_tile_dup, dim3(blocks(n_tiles)), dim3(T), 0, st, tile_list, n_tiles, nall, L.tile_pos,
+  hipLaunchKernelGGL(k_tile_pos_fix, dim3(blocks(most)), dim3(T), 0, st, tile_list, n_tiles, nall, L.tile_pos,
                      tile_status);
-  hipLaunchKernelGGL(k_tile_pos_fix, dim3(blocks(nall)), dim3(T), 0, st, L.tile_pos, nall);
   LS_LAUNCH_CHECK();
 
   BinParams bp;
