@@ -51,7 +51,7 @@ constexpr int MAXG = 76;                 // max buckets per side
 constexpr int MAXB = MAXG * MAXG;        // max buckets
 static_assert(2 * (MAXB + 1) <= PREP_INTS, "bucket offsets must fit twice in the preparation's LDS");
 constexpr int TB = 256;                  // threads of a star or output workgroup
-constexpr int OUT_INTS = 9600;           // LDS of an output workgroup for the points and bucket offsets
+constexpr int OUT_INTS = 7000;           // LDS of an output workgroup for the points and bucket offsets
 constexpr int ITEM_MIN = 8, ITEM_MAX = 16;  // points of a work item of the stars
 constexpr int CAND = 8;                  // candidates of a star a lane holds
 constexpr int CANDS = 8 * CAND;          // and the eight lanes of a star
@@ -62,7 +62,7 @@ constexpr uint64_t FACE_NONE = ~0ull;
 // length beside the midpoint, its half side this share, at least SEARCH_MIN buckets
 constexpr float SEARCH_OFFSET = 0.5f, SEARCH_SIZE = 0.9f, SEARCH_MIN = 0.6f;
 // First margin, in buckets, of a nearest-point search
-constexpr float NEAR_MARGIN = 0.8f;
+constexpr float NEAR_MARGIN = 1.f;
 constexpr int SORT_LDS = 16384;          // bin segments up to this size sort in LDS
 
 struct BinParams {
@@ -345,8 +345,7 @@ struct ReconParams {
   uint64_t* skey;
   int32_t* sidx;
   int2* cuv;
-  int32_t* cz;
-  uint64_t* crgb;  // R | G << 16 | B << 32
+  int4* cattr;  // z, R, G, B
   int32_t* boff;   // 2 per bin entry: canonical bucket offsets of a tile from 2 * its bin offset on
   // per tile slot
   int32_t* npts;   // canonical points
@@ -374,20 +373,13 @@ __device__ __forceinline__ int bucket_side(int cnt) {
 // flat loads, which wait on both the LDS and the vector-memory counters).
 typedef const __attribute__((address_space(3))) int32_t* LdsI32;
 typedef const __attribute__((address_space(3))) uint64_t* LdsU64;
-// Point coordinates (u, v) as one 8-byte read, from LDS or global memory.
-struct UvLds {
-  LdsU64 p;
-  __device__ __forceinline__ int2 operator[](int i) const {
-    const uint64_t w = p[i];
-    return make_int2((int)(uint32_t)w, (int)(uint32_t)(w >> 32));
-  }
-};
+// Point coordinates (u, v) as one 8-byte read.
 struct UvGlobal {
   const int2* p;
   __device__ __forceinline__ int2 operator[](int i) const { return p[i]; }
 };
 
-// A tile's canonical points: coordinates through UVP (UvLds or UvGlobal),
+// A tile's canonical points: coordinates through UVP (UvGlobal or one of the Uvf),
 // bucket offsets (G * G + 1, row-major) through BP.
 template <class UVP, class BP>
 struct TileT {
@@ -457,49 +449,6 @@ __device__ __forceinline__ int incircle_sos(int a, int b, int c, int d, int2 pa,
   const double perm = fabs(t1) + fabs(t2) + fabs(t3);
   if (fabs(det) > 8.8817841970012523e-16 * perm) return sgn_d(det);  // 8 * 2^-53
   return incircle_exact(a, b, c, d, pa, pb, pc, pd);
-}
-
-// Nearest points of an 8 x 8 block of texels, one texel per lane of a wave;
-// ties go to the smallest (d^2, v, u).  The 16 lanes of a 4 x 4 texel
-// sub-block scan the same buckets, those under the sub-block widened by a
-// margin, so their loop is uniform and a point is one LDS broadcast; the
-// margin grows until it covers the distance of every lane's answer, which
-// proves it.  (i, j) is the lane's texel, inside the grid for every lane that
-// counts.
-template <class TT>
-__device__ int nearest_of_texel(const TT& T, int q0, int C, int R, int i0, int j0, int i, int j) {
-  const int qx = q0 + j * C, qy = q0 + i * C;
-  const bool in_grid = i < R && j < R;
-  const float gx0 = (float)(q0 + j0 * C + T.H) * T.inv, gx1 = (float)(q0 + min(j0 + 3, R - 1) * C + T.H) * T.inv;
-  const float gy0 = (float)(q0 + i0 * C + T.H) * T.inv, gy1 = (float)(q0 + min(i0 + 3, R - 1) * C + T.H) * T.inv;
-  float r = NEAR_MARGIN;
-  int best = -1;
-  double bd = 1e300;  // squared distance, exact in double (below 2^40)
-  for (;;) {
-    const int x0 = max((int)floorf(gx0 - r), 0), x1 = min((int)floorf(gx1 + r), T.G - 1);
-    const int y0 = max((int)floorf(gy0 - r), 0), y1 = min((int)floorf(gy1 + r), T.G - 1);
-    for (int y = y0; y <= y1; ++y) {
-      const int e = T.boff[y * T.G + x1 + 1];
-      for (int p = T.boff[y * T.G + x0]; p < e; ++p) {
-        const int2 P = T.uv[p];
-        const double dx = P.x - qx, dy = P.y - qy;
-        const double d = fma(dx, dx, dy * dy);
-        bool less = d < bd;
-        if (d == bd) {  // rare: two points at the same distance (or the same point again)
-          const int2 Q = T.uv[best];
-          less = P.y < Q.y || (P.y == Q.y && P.x < Q.x);
-        }
-        bd = less ? d : bd;
-        best = less ? p : best;
-      }
-    }
-    float need = !in_grid ? 0.f : (best >= 0 ? sqrtf((float)bd) * T.inv * 1.000001f + 1e-3f : 2.f * r);
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) need = fmaxf(need, __shfl_xor(need, o, 64));
-    if (need <= r || (x0 == 0 && y0 == 0 && x1 == T.G - 1 && y1 == T.G - 1)) break;
-    r = need;
-  }
-  return best;
 }
 
 // ---- stars: a group of eight lanes works on one star
@@ -604,6 +553,94 @@ __device__ __forceinline__ int nearest_of_point(const TT& T, int a, int gl) {
     const float need = best != INT_MAX ? sqrtf((float)bd) * T.inv * 1.000001f + 1e-3f : 2.f * r;
     if ((best != INT_MAX && need <= r) || (x0 == 0 && y0 == 0 && x1 == T.G - 1 && y1 == T.G - 1)) return best;
     r = need;
+  }
+}
+
+// Coordinates of a tile's points as floats (exact, below 2^18), from LDS with
+// three far points behind the last, or from global memory, where an index
+// behind the last reads that.
+struct UvfLds {
+  LdsU64 p;
+  __device__ __forceinline__ float2 operator[](int i) const { return __builtin_bit_cast(float2, (uint64_t)p[i]); }
+};
+struct UvfGlobal {
+  const int2* p;
+  int last;
+  __device__ __forceinline__ float2 operator[](int i) const {
+    const int2 P = p[min(i, last)];
+    return make_float2((float)P.x, (float)P.y);
+  }
+};
+
+// Nearest points of an 8 x 8 block of texels, one texel per lane of a wave;
+// ties go to the smallest (d^2, v, u).  The 16 lanes of a 4 x 4 texel
+// sub-block scan the same buckets, those under the sub-block widened by a
+// margin, so their loop is uniform and a point is one LDS broadcast; the
+// margin grows until it covers the distance of every lane's answer, which
+// proves it.  (i, j) is the lane's texel, inside the grid for every lane that
+// counts.
+//
+// Distances are taken in float (differences exact, squares within 1.2e-7), four
+// points at a time without a branch, also those behind the end of a bucket row
+// where it is no multiple of four; a lane whose two least are closer than
+// NEAR_TIE compares the points within it exactly.
+constexpr float NEAR_TIE = 5e-7f;
+template <class TT>
+__device__ __forceinline__ int nearest_of_texel(const TT& T, int q0, int C, int R, int i0, int j0, int i, int j) {
+  const int qx = q0 + j * C, qy = q0 + i * C;
+  const float fqx = (float)qx, fqy = (float)qy;
+  const bool in_grid = i < R && j < R;
+  const float gx0 = (float)(q0 + j0 * C + T.H) * T.inv, gx1 = (float)(q0 + min(j0 + 3, R - 1) * C + T.H) * T.inv;
+  const float gy0 = (float)(q0 + i0 * C + T.H) * T.inv, gy1 = (float)(q0 + min(i0 + 3, R - 1) * C + T.H) * T.inv;
+  float r = NEAR_MARGIN;
+  for (;;) {
+    const int x0 = max((int)floorf(gx0 - r), 0), x1 = min((int)floorf(gx1 + r), T.G - 1);
+    const int y0 = max((int)floorf(gy0 - r), 0), y1 = min((int)floorf(gy1 + r), T.G - 1);
+    int best = -1;
+    float bd = 3e38f, second = 3e38f;  // the two least squared distances
+    for (int y = y0; y <= y1; ++y) {
+      const int e = T.boff[y * T.G + x1 + 1];
+      for (int p = T.boff[y * T.G + x0]; p < e; p += 4) {
+        float2 P[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) P[k] = T.uv[p + k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float dx = P[k].x - fqx, dy = P[k].y - fqy;
+          const float d = fmaf(dx, dx, dy * dy);
+          second = fminf(second, fmaxf(bd, d));
+          best = d < bd ? p + k : best;
+          bd = fminf(bd, d);
+        }
+      }
+    }
+    float need = !in_grid ? 0.f : (best >= 0 ? sqrtf(bd) * T.inv * 1.000001f + 1e-3f : 2.f * r);
+    need = group_reduce(need, [](float a, float b) { return fmaxf(a, b); });
+    need = fmaxf(need, row_move<0x128>(need));  // the other eight lanes
+    if (need > r && !(x0 == 0 && y0 == 0 && x1 == T.G - 1 && y1 == T.G - 1)) {
+      r = need;
+      continue;
+    }
+    if (second <= bd + bd * NEAR_TIE) {
+      const float lim = bd + bd * NEAR_TIE;
+      double ed = 1e300;  // squared distance, exact in double (below 2^40)
+      float2 E = make_float2(0.f, 0.f);
+      for (int y = y0; y <= y1; ++y) {
+        const int e = T.boff[y * T.G + x1 + 1];
+        for (int p = T.boff[y * T.G + x0]; p < e; ++p) {
+          const float2 P = T.uv[p];
+          const float dx = P.x - fqx, dy = P.y - fqy;
+          if (fmaf(dx, dx, dy * dy) > lim) continue;
+          const double d = fma((double)dx, (double)dx, (double)dy * (double)dy);
+          if (d < ed || (d == ed && (P.y < E.y || (P.y == E.y && P.x < E.x)))) {
+            ed = d;
+            E = P;
+            best = p;
+          }
+        }
+      }
+    }
+    return best;
   }
 }
 
@@ -1025,8 +1062,7 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
           P.cuv[w] = make_int2((int)(uint32_t)kk - (1 << 20), (int)(uint32_t)(kk >> 32) - (1 << 20));
           const int32_t gi = P.bin_idx[off + idx[i]];
           const uint16_t* c3 = P.rgb + 3 * (int64_t)gi;
-          P.cz[w] = P.z[gi];
-          P.crgb[w] = (uint64_t)c3[0] | ((uint64_t)c3[1] << 16) | ((uint64_t)c3[2] << 32);
+          P.cattr[w] = make_int4(P.z[gi], c3[0], c3[1], c3[2]);
           ++w;
         }
     }
@@ -1356,6 +1392,10 @@ __global__ void __launch_bounds__(TB, 3) k_recon_stars(ReconParams P) {
 
 // Phases d-e, `parts` workgroups per tile: nearest point of every texel,
 // interpolation, normalisation and output, 8 x 8 texels per wave at a time.
+// Bound by instruction issue (the 1024-tile batch's 302 MB leave in 217 us, at
+// the rate of a fill in 45).  Heights and colours are read from global memory,
+// one 16-byte record a point: in LDS with the coordinates they left three waves
+// per SIMD (now five), which with the nearest points in double took 407 us.
 __global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
   __shared__ __align__(16) int s_mem[OUT_INTS];
   __shared__ double s_cz, s_d[TB];
@@ -1370,25 +1410,21 @@ __global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
   const int R = P.R, C = P.C;
   const int G = bucket_side(cnt), NB = G * G;
   const uint64_t* __restrict__ fm = P.facemap + (int64_t)pos * R * R;
-  const bool uv_lds = 2 * m + NB + 1 <= OUT_INTS;
-  const bool attr_lds = 5 * m + NB + 1 <= OUT_INTS;
-  // colours and coordinates (8 bytes each), heights, bucket offsets
-  uint64_t* s_c = reinterpret_cast<uint64_t*>(s_mem + 2 * m);
-  int32_t* s_z = s_mem + 4 * m;
-  int32_t* s_off = s_mem + (attr_lds ? 5 * m : 2 * m);
-  if (uv_lds) {
-    int2* uv = reinterpret_cast<int2*>(s_mem);
+  // coordinates, three far points, bucket offsets
+  const bool lds = 2 * (m + 3) + NB + 1 <= OUT_INTS;
+  int32_t* s_off = s_mem + 2 * (m + 3);
+  if (lds) {
+    float2* uv = reinterpret_cast<float2*>(s_mem);
     for (int p = tid; p < m; p += TB) {
-      uv[p] = P.cuv[off + p];
-      if (attr_lds) {
-        s_c[p] = P.crgb[off + p];
-        s_z[p] = P.cz[off + p];
-      }
+      const int2 Q = P.cuv[off + p];
+      uv[p] = make_float2((float)Q.x, (float)Q.y);
     }
+    if (tid < 3) uv[m + tid] = make_float2(1e9f, 1e9f);
     for (int b = tid; b <= NB; b += TB) s_off[b] = P.boff[2 * (int64_t)off + b];
   }
   __syncthreads();
-  auto run = [&](auto uvp, auto bp, auto Tz, auto Tc) {
+  const int4* __restrict__ attr = P.cattr + off;
+  auto run = [&](auto uvp, auto bp) {
     TileT<decltype(uvp), decltype(bp)> T;
     T.uv = uvp;
     T.boff = bp;
@@ -1399,31 +1435,27 @@ __global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
     const int q0 = -P.H + C / 2;
     // height (metres) and colours of texel (i, j): linear in its triangle, or
     // its nearest point's
-    auto lin_value = [&](int i, int j, uint64_t f, int p, double* out4) {
+    auto lin_value = [&](int i, int j, uint64_t f, int4 near, double* out4) {
       if (f == FACE_NONE) {
-        out4[0] = (double)Tz[p] * P.scale_z + P.offset_z;
-        const uint64_t c = Tc[p];
-        out4[1] = (double)(c & 0xFFFF);
-        out4[2] = (double)((c >> 16) & 0xFFFF);
-        out4[3] = (double)((c >> 32) & 0xFFFF);
+        out4[0] = (double)near.x * P.scale_z + P.offset_z;
+        out4[1] = near.y;
+        out4[2] = near.z;
+        out4[3] = near.w;
         return;
       }
       const int a = (int)(f >> 42), b = (int)((f >> 21) & 0x1FFFFF), c = (int)(f & 0x1FFFFF);
-      const int2 A = T.uv[a], B = T.uv[b], Cc = T.uv[c];
+      const float2 A = T.uv[a], B = T.uv[b], Cc = T.uv[c];
+      const int4 va = attr[a], vb = attr[b], vc = attr[c];
       const double qx = q0 + j * C, qy = q0 + i * C;
       const double ob = orient_d(Cc.x, Cc.y, A.x, A.y, qx, qy);
       const double oc = orient_d(A.x, A.y, B.x, B.y, qx, qy);
       const double O = orient_d(A.x, A.y, B.x, B.y, Cc.x, Cc.y);
       const double lb = ob / O, lc = oc / O;
-      const double za = Tz[a], zb = Tz[b], zc = Tz[c];
-      const double h = za + lb * (zb - za) + lc * (zc - za);
-      out4[0] = h * P.scale_z + P.offset_z;
-      const uint64_t ca = Tc[a], cb = Tc[b], cc = Tc[c];
-      for (int ch = 0; ch < 3; ++ch) {
-        const double va = (double)((ca >> (16 * ch)) & 0xFFFF), vb = (double)((cb >> (16 * ch)) & 0xFFFF),
-                     vc = (double)((cc >> (16 * ch)) & 0xFFFF);
-        out4[1 + ch] = va + lb * (vb - va) + lc * (vc - va);
-      }
+      auto mix = [&](double x, double y, double z) { return x + lb * (y - x) + lc * (z - x); };
+      out4[0] = mix(va.x, vb.x, vc.x) * P.scale_z + P.offset_z;
+      out4[1] = mix(va.y, vb.y, vc.y);
+      out4[2] = mix(va.z, vb.z, vc.z);
+      out4[3] = mix(va.w, vb.w, vc.w);
     };
     // c_z: the centre texel; outside the hull (sparse windows) its nearest
     // point is searched by all lanes
@@ -1435,12 +1467,12 @@ __global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
       double bd = 1e300;
       auto less = [&](double d, int p, double d2, int p2) -> bool {
         if (p2 < 0 || d != d2) return p2 < 0 || d < d2;
-        const int2 A = T.uv[p], B = T.uv[p2];
+        const float2 A = T.uv[p], B = T.uv[p2];
         return A.y < B.y || (A.y == B.y && A.x < B.x);
       };
       for (int p = tid; p < m; p += TB) {
-        const int2 Q = T.uv[p];
-        const double dx = Q.x - qc, dy = Q.y - qc;
+        const float2 Q = T.uv[p];
+        const double dx = (double)Q.x - qc, dy = (double)Q.y - qc;
         const double d = fma(dx, dx, dy * dy);
         if (less(d, p, bd, pc)) {
           bd = d;
@@ -1459,7 +1491,7 @@ __global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
     }
     if (tid == 0) {
       double v4[4];
-      lin_value(ic, ic, fc, pc, v4);
+      lin_value(ic, ic, fc, attr[max(pc, 0)], v4);
       s_cz = v4[0];
       if (part == 0) P.cz_out[k] = v4[0];
     }
@@ -1476,26 +1508,22 @@ __global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
       const uint64_t f = in_grid ? fm[i * R + j] : FACE_NONE;
       const int p = nearest_of_texel(T, q0, C, R, min(i0, R - 1), min(j0, R - 1), i, j);
       if (!in_grid) continue;
+      const int4 near = attr[p];
       double lv[4];
-      lin_value(i, j, f, p, lv);
-      const double hn = (double)Tz[p] * P.scale_z + P.offset_z;
-      const uint64_t c = Tc[p];
+      lin_value(i, j, f, near, lv);
+      const double hn = (double)near.x * P.scale_z + P.offset_z;
       const double k65 = 1.0 / 65535.0;
       const int tt = i * R + j;
       out[2 * tt] = make_float4((float)((lv[0] - cz) * P.inv_r), (float)((hn - cz) * P.inv_r), (float)(lv[1] * k65),
                                 (float)(lv[2] * k65));
-      out[2 * tt + 1] = make_float4((float)(lv[3] * k65), (float)((double)(c & 0xFFFF) * k65),
-                                    (float)((double)((c >> 16) & 0xFFFF) * k65),
-                                    (float)((double)((c >> 32) & 0xFFFF) * k65));
+      out[2 * tt + 1] = make_float4((float)(lv[3] * k65), (float)((double)near.y * k65), (float)((double)near.z * k65),
+                                    (float)((double)near.w * k65));
     }
   };
-  if (attr_lds)
-    run(UvLds{(LdsU64)s_mem}, (LdsI32)s_off, (LdsI32)s_z, (LdsU64)s_c);
-  else if (uv_lds)
-    run(UvLds{(LdsU64)s_mem}, (LdsI32)s_off, (const int32_t*)(P.cz + off), (const uint64_t*)(P.crgb + off));
+  if (lds)
+    run(UvfLds{(LdsU64)s_mem}, (LdsI32)s_off);
   else
-    run(UvGlobal{P.cuv + off}, (const int32_t*)(P.boff + 2 * (int64_t)off), (const int32_t*)(P.cz + off),
-        (const uint64_t*)(P.crgb + off));
+    run(UvfGlobal{P.cuv + off, m - 1}, (const int32_t*)(P.boff + 2 * (int64_t)off));
 }
 
 int g_num_cu = 0;
@@ -1520,8 +1548,9 @@ struct ReconLayout {
   int32_t* bin_off;
   int32_t* bin_idx;
   int32_t* sort_scratch;
-  int32_t *su, *sv, *sslot, *sidx, *cz;
-  uint64_t *skey, *crgb;
+  int32_t *su, *sv, *sslot, *sidx;
+  uint64_t* skey;
+  int4* cattr;
   int2* cuv;
   uint64_t* facemap;
   int64_t face_tiles;  // tiles whose face maps fit
@@ -1587,9 +1616,8 @@ void recon_layout(const LsGridInfo& gi, int32_t n_tiles, int64_t n, void* base, 
   L->sv = A.take<int32_t>(E);
   L->sslot = A.take<int32_t>(E);
   L->sidx = A.take<int32_t>(E);
-  L->cz = A.take<int32_t>(E);
   L->skey = A.take<uint64_t>(E);
-  L->crgb = A.take<uint64_t>(E);
+  L->cattr = A.take<int4>(E);
   L->cuv = A.take<int2>(E);
   L->items = A.take<int2>(E / 3 + 1);
   L->entries = E;
@@ -1704,8 +1732,7 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
   rp.skey = L.skey;
   rp.sidx = L.sidx;
   rp.cuv = L.cuv;
-  rp.cz = L.cz;
-  rp.crgb = L.crgb;
+  rp.cattr = L.cattr;
   rp.boff = L.sort_scratch;  // free once the caller's CSR is sorted
   rp.npts = L.fill;          // free once the points are binned
   rp.has_dt = L.counts;
