@@ -35,9 +35,9 @@
 // Three launches rather than one workgroup per tile from end to end: the work
 // of a tile follows its point count (20 to tens of thousands), and a launch
 // over runs of points spreads the largest tile over the chip.  One tile of 400
-// points 535 -> 204 us (reconstruction and network), one of 16,000 points
-// 16.3 -> 0.75 ms, 1024 tiles of 50-2000 points 2.23 -> 1.82 ms, 16384 tiles of
-// 20-5000 points 12.7 -> 8.9 ms.
+// points 542 -> 194 us (reconstruction and network), one of 16,000 points
+// 16.3 -> 0.78 ms, 1024 tiles of 50-2000 points 2.22 -> 1.54 ms, 16384 tiles of
+// 20-5000 points 12.5 -> 7.9 ms.
 #include <algorithm>
 #include <mutex>
 
@@ -52,6 +52,9 @@ constexpr int MAXB = MAXG * MAXG;        // max buckets
 static_assert(2 * (MAXB + 1) <= PREP_INTS, "bucket offsets must fit twice in the preparation's LDS");
 constexpr int TB = 256;                  // threads of a star or output workgroup
 constexpr int OUT_INTS = 7000;           // LDS of an output workgroup for the points and bucket offsets
+constexpr int XCDS = 8;                  // chiplets, each with an L2 of its own
+constexpr int ITEM_COUNTER = 32;         // integers from a counter to the next: a cache line each
+constexpr int N_FLAGS = ITEM_COUNTER * (2 + XCDS);
 constexpr int ITEM_MIN = 8, ITEM_MAX = 16;  // points of a work item of the stars
 constexpr int CAND = 8;                  // candidates of a star a lane holds
 constexpr int CANDS = 8 * CAND;          // and the eight lanes of a star
@@ -131,7 +134,7 @@ __global__ void k_recon_init(int32_t* __restrict__ tile_pos, int64_t n_all, int3
     fill[i] = 0;
     if (i < n_tiles) status[i] = 0;
   }
-  if (first < 4) flags[first] = 0;
+  for (int64_t i = first; i < N_FLAGS; i += step) flags[i] = 0;
 }
 
 __global__ void k_tile_pos(const int32_t* __restrict__ tile_list, int32_t n_tiles, int64_t n_all,
@@ -352,7 +355,7 @@ struct ReconParams {
   int32_t* has_dt; // 1: at least three points, not all collinear
   uint64_t* facemap;  // R * R texels of every tile of the launch
   int2* items;        // work items of the stars: position of the tile in the launch, first point
-  int32_t* item_n;    // how many, and how many are taken
+  int32_t* item_n;    // how many, then by XCD how many of its range are taken, ITEM_COUNTER apart
   int32_t item;       // points of an item
   const int32_t* order;  // processing position -> tile slot
   int32_t q0;            // first position of the launch
@@ -452,7 +455,7 @@ __device__ __forceinline__ int incircle_sos(int a, int b, int c, int d, int2 pa,
 }
 
 // ---- stars: a group of eight lanes works on one star
-constexpr int STAR_LANES = 8;
+constexpr int STAR_LANES = 8;  // as many as RASTER_LANES
 template <int CTRL>
 __device__ __forceinline__ int row_move(int v) {
   return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
@@ -668,17 +671,32 @@ struct Rect {
   float x0, x1, y0, y1;
 };
 
+// Where a better point than one of cotangent t can lie, relative to the edge's
+// first point, for an edge (ex, ey) of length len: the circle through the edge
+// and that point, of which only the part left of the edge counts (for a centre
+// on the right the thin cap between the chord and the parallel tangent).  With n
+// the edge turned left by 90 degrees, the circle's centre is mid + n t / 2 and
+// its radius |n| sqrt(1 + t^2) / 2.
+__device__ __forceinline__ Rect circle_box(float ex, float ey, float len, float t) {
+  const float u = sqrtf(1.f + t * t);
+  if (t > 0.f) {
+    const float ox = 0.5f * (ex - t * ey), oy = 0.5f * (ey + t * ex), rho = 0.5f * len * u;
+    const float mg = 1e-3f + 2e-6f * rho;
+    return Rect{ox - rho - mg, ox + rho + mg, oy - rho - mg, oy + rho + mg};
+  }
+  const float k = 0.5f / (u - t);  // height of the cap over |n|
+  const float nx = -k * ey, ny = k * ex;
+  return Rect{fminf(ex, 0.f) + fminf(nx, 0.f) - 1e-3f, fmaxf(ex, 0.f) + fmaxf(nx, 0.f) + 1e-3f,
+              fminf(ey, 0.f) + fminf(ny, 0.f) - 1e-3f, fmaxf(ey, 0.f) + fmaxf(ny, 0.f) + 1e-3f};
+}
+
 // The search by the lanes of a group.  `best` is the first point met
 // among the points of `known` (-1: none there), an empty rectangle if none was
 // looked at.
 //
 // The points are scanned by bucket rows of a square beside the edge that
-// doubles until it holds every place a better point could be: the circle
-// through a, b and the best point so far, of which only the part left of the
-// edge counts (for a centre on the right the thin cap between the chord and
-// the parallel tangent).  With t the best cotangent and n the edge turned left
-// by 90 degrees, the circle's centre is mid + n t / 2 and its radius
-// |n| sqrt(1 + t^2) / 2.  Squares and circles only bound the search, in float
+// grows until it holds every place a better point than the best so far could
+// be (circle_box).  Squares and circles only bound the search, in float
 // and in units of buckets, with margins far above the float rounding (2e-5
 // buckets at 76 buckets a side); each row is also cut at the edge's line.
 template <class TT>
@@ -708,24 +726,8 @@ __device__ __forceinline__ int third_left(const TT& T, int a, int b, int best, R
   };
   float cot = best >= 0 ? cot_of(T.uv[best]) : COT_NONE;
   auto narrow = [&]() {
-    const float t = cot, u = sqrtf(1.f + t * t);
-    float x0, x1, y0, y1, mg = 1e-3f;
-    if (t > 0.f) {
-      const float ox = mx - 0.5f * t * fey, oy = my + 0.5f * t * fex, rho = 0.5f * len * u;
-      mg += 2e-6f * rho;
-      x0 = ox - rho;
-      x1 = ox + rho;
-      y0 = oy - rho;
-      y1 = oy + rho;
-    } else {
-      const float k = 0.5f / (u - t);  // height of the cap over |n|
-      const float nx = -k * fey, ny = k * fex;
-      x0 = fminf(fax, fax + fex) + fminf(nx, 0.f);
-      x1 = fmaxf(fax, fax + fex) + fmaxf(nx, 0.f);
-      y0 = fminf(fay, fay + fey) + fminf(ny, 0.f);
-      y1 = fmaxf(fay, fay + fey) + fmaxf(ny, 0.f);
-    }
-    box = Rect{fmaxf(box.x0, x0 - mg), fminf(box.x1, x1 + mg), fmaxf(box.y0, y0 - mg), fminf(box.y1, y1 + mg)};
+    const Rect c = circle_box(fex, fey, len, cot);
+    box = Rect{fmaxf(box.x0, fax + c.x0), fminf(box.x1, fax + c.x1), fmaxf(box.y0, fay + c.y0), fminf(box.y1, fay + c.y1)};
   };
   if (best >= 0) {
     narrow();
@@ -831,58 +833,113 @@ __device__ __forceinline__ void texel_range(int lo, int hi, int H, int C, int R,
   if (j1 > R - 1) j1 = R - 1;
 }
 
-// Texel bounding box of triangle (a, b, c); false when it holds no texel.
+// A triangle to rasterise: the box of its texels and its three edge functions,
+// e + di * i + dj * j at the box's texel (di, dj).  These are integers below
+// 2^53, so stepping them over the box is exact; the top-left rule for a texel on
+// an edge is a half unit added or taken off, so a texel is inside where all
+// three are positive.
+struct RasterTri {
+  double ea, ai, aj, eb, bi, bj, ec, ci, cj;
+  int i0, j0, h, w;  // w 0: no texel
+  uint64_t key;
+  __device__ __forceinline__ bool inside(double di, double dj) const {
+    return fma(di, ai, fma(dj, aj, ea)) > 0. && fma(di, bi, fma(dj, bj, eb)) > 0. && fma(di, ci, fma(dj, cj, ec)) > 0.;
+  }
+};
+
 template <class TT>
-__device__ __forceinline__ bool tri_texel_box(const TT& T, int a, int b, int c, int C, int R, int& i0, int& i1,
-                                              int& j0, int& j1) {
-  const int2 A = T.uv[a], B = T.uv[b], Cc = T.uv[c];
-  texel_range(min(A.x, min(B.x, Cc.x)), max(A.x, max(B.x, Cc.x)), T.H, C, R, j0, j1);
-  texel_range(min(A.y, min(B.y, Cc.y)), max(A.y, max(B.y, Cc.y)), T.H, C, R, i0, i1);
-  return i0 <= i1 && j0 <= j1;
+__device__ __forceinline__ RasterTri raster_tri(const TT& T, uint64_t key, int C, int R) {
+  RasterTri t;
+  const int2 A = T.uv[(int)(key >> 42)], B = T.uv[(int)((key >> 21) & 0x1FFFFF)], Cc = T.uv[(int)(key & 0x1FFFFF)];
+  const int ax = A.x, ay = A.y, bx = B.x, by = B.y, cx = Cc.x, cy = Cc.y;
+  int i1, j1;
+  texel_range(min(ax, min(bx, cx)), max(ax, max(bx, cx)), T.H, C, R, t.j0, j1);
+  texel_range(min(ay, min(by, cy)), max(ay, max(by, cy)), T.H, C, R, t.i0, i1);
+  t.key = key;
+  t.h = i1 - t.i0 + 1;
+  t.w = t.h > 0 ? max(j1 - t.j0 + 1, 0) : 0;
+  const double qx = -T.H + C / 2 + t.j0 * C, qy = -T.H + C / 2 + t.i0 * C;  // the box's first texel
+  t.ea = orient_d(bx, by, cx, cy, qx, qy) + (edge_owned(bx, by, cx, cy) ? 0.5 : -0.5);
+  t.eb = orient_d(cx, cy, ax, ay, qx, qy) + (edge_owned(cx, cy, ax, ay) ? 0.5 : -0.5);
+  t.ec = orient_d(ax, ay, bx, by, qx, qy) + (edge_owned(ax, ay, bx, by) ? 0.5 : -0.5);
+  const double C_d = C;
+  t.ai = (cx - bx) * C_d;
+  t.aj = (by - cy) * C_d;
+  t.bi = (ax - cx) * C_d;
+  t.bj = (cy - ay) * C_d;
+  t.ci = (bx - ax) * C_d;
+  t.cj = (ay - by) * C_d;
+  return t;
+}
+
+// e / d and the remainder from a float estimate (e < 2^24), corrected exactly.
+__device__ __forceinline__ void divide_small(int e, int d, float rd, int& q, int& r) {
+  q = (int)((float)e * rd);
+  r = e - q * d;
+  q += (r >= d) - (r < 0);
+  r = e - q * d;
 }
 
 // Triangles are not rasterised by the lanes that find them but by groups of this
-// many lanes, so rasterisation does not hold up the walks.
+// many lanes, so rasterisation does not hold up the walks; triangles whose box
+// has more texels than RASTER_MAX are left to the whole wave.
 constexpr int RASTER_LANES = 8;
-constexpr int RASTER_MAX = 64;  // texels of a box they take; larger ones are left to the whole wave
+constexpr int RASTER_MAX = 64;
 
 // Write the triangle into every texel whose centre lies in it under the top-left
-// rule, by LANES lanes; false, and nothing written, if its box has more than
-// `most` texels.  Every texel of the box gets the exact test.  The three edge
-// functions are integers below 2^53, so stepping them over the box is exact;
-// an edge's ownership of the texels on it is a threshold half a unit below or
-// above zero.
-template <int LANES, class TT>
-__device__ bool raster_triangle(const TT& T, uint64_t key, int C, int R, uint64_t* __restrict__ fm, int lane, int most) {
-  const int a = (int)(key >> 42), b = (int)((key >> 21) & 0x1FFFFF), c = (int)(key & 0x1FFFFF);
-  int i0, i1, j0, j1;
-  if (!tri_texel_box(T, a, b, c, C, R, i0, i1, j0, j1)) return true;
-  if ((i1 - i0 + 1) * (j1 - j0 + 1) > most) return false;
-  const int2 A = T.uv[a], B = T.uv[b], Cc = T.uv[c];
-  const int ax = A.x, ay = A.y, bx = B.x, by = B.y, cx = Cc.x, cy = Cc.y;
-  const double ta = edge_owned(bx, by, cx, cy) ? -0.5 : 0.5, tb = edge_owned(cx, cy, ax, ay) ? -0.5 : 0.5,
-               tc = edge_owned(ax, ay, bx, by) ? -0.5 : 0.5;
-  const double qx = -T.H + C / 2 + j0 * C, qy = -T.H + C / 2 + i0 * C;  // the box's first texel
-  const double ea = orient_d(bx, by, cx, cy, qx, qy), eb = orient_d(cx, cy, ax, ay, qx, qy),
-               ec = orient_d(ax, ay, bx, by, qx, qy);
-  const double C_d = C;
-  const double ai = (cx - bx) * C_d, aj = (by - cy) * C_d, bi = (ax - cx) * C_d, bj = (cy - ay) * C_d,
-               ci = (bx - ax) * C_d, cj = (ay - by) * C_d;
-  const int w = j1 - j0 + 1, n = (i1 - i0 + 1) * w;
-  const float rw = __builtin_amdgcn_rcpf((float)w);
-  for (int e = lane; e < n; e += LANES) {
-    // e / w from a float estimate (e < 2^24), corrected exactly
-    int di = (int)((float)e * rw);
-    if (di * w > e)
-      --di;
-    else if ((di + 1) * w <= e)
-      ++di;
-    const int dj = e - di * w;
-    const double fi = di, fj = dj;
-    if (fma(fi, ai, fma(fj, aj, ea)) > ta && fma(fi, bi, fma(fj, bj, eb)) > tb && fma(fi, ci, fma(fj, cj, ec)) > tc)
-      fm[(i0 + di) * R + j0 + dj] = key;
+// rule, by a group of lanes: every texel of the box gets the exact test.
+__device__ __forceinline__ void raster_box(const RasterTri& t, int R, uint64_t* __restrict__ fm, int lane) {
+  const float rw = __builtin_amdgcn_rcpf((float)t.w);
+  for (int e = lane; e < t.h * t.w; e += RASTER_LANES) {
+    int di, dj;
+    divide_small(e, t.w, rw, di, dj);
+    if (t.inside(di, dj)) fm[(t.i0 + di) * R + t.j0 + dj] = t.key;
   }
-  return true;
+}
+
+// The same for the triangle of lane src, by the whole wave: 8 x 8 texels at a
+// time, without those beyond one of the edges (the slivers along the hull of a
+// sparse window have boxes of thousands of texels).
+__device__ __forceinline__ void raster_wave(const RasterTri& of, int src, int R, uint64_t* __restrict__ fm, int lane) {
+  auto get = [&](int v) -> int { return __builtin_amdgcn_readlane(v, src); };
+  auto get_d = [&](double v) -> double {
+    const uint64_t w = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)(uint32_t)get((int)(uint32_t)w) |
+                                          ((uint64_t)(uint32_t)get((int)(uint32_t)(w >> 32)) << 32));
+  };
+  RasterTri t;
+  t.ea = get_d(of.ea);
+  t.ai = get_d(of.ai);
+  t.aj = get_d(of.aj);
+  t.eb = get_d(of.eb);
+  t.bi = get_d(of.bi);
+  t.bj = get_d(of.bj);
+  t.ec = get_d(of.ec);
+  t.ci = get_d(of.ci);
+  t.cj = get_d(of.cj);
+  t.i0 = get(of.i0);
+  t.j0 = get(of.j0);
+  t.h = get(of.h);
+  t.w = get(of.w);
+  t.key = __builtin_bit_cast(uint64_t, get_d(__builtin_bit_cast(double, of.key)));
+  // the largest value of an edge function over a block: at one of its corners
+  const double ma = t.ea + fmax(7 * t.ai, 0.) + fmax(7 * t.aj, 0.), mb = t.eb + fmax(7 * t.bi, 0.) + fmax(7 * t.bj, 0.),
+               mc = t.ec + fmax(7 * t.ci, 0.) + fmax(7 * t.cj, 0.);
+  const int nbj = (t.w + 7) / 8, nb = nbj * ((t.h + 7) / 8);
+  const float rn = __builtin_amdgcn_rcpf((float)nbj);
+  for (int b0 = 0; b0 < nb; b0 += 64) {
+    int q, r;
+    divide_small(b0 + lane, nbj, rn, q, r);
+    const double di = 8 * q, dj = 8 * r;
+    uint64_t near = __ballot(b0 + lane < nb && fma(di, t.ai, fma(dj, t.aj, ma)) > 0. &&
+                             fma(di, t.bi, fma(dj, t.bj, mb)) > 0. && fma(di, t.ci, fma(dj, t.cj, mc)) > 0.);
+    for (; near; near &= near - 1) {
+      const int blk = __builtin_ctzll(near);
+      const int ti = 8 * __builtin_amdgcn_readlane(q, blk) + (lane >> 3);
+      const int tj = 8 * __builtin_amdgcn_readlane(r, blk) + (lane & 7);
+      if (ti < t.h && tj < t.w && t.inside(ti, tj)) fm[(t.i0 + ti) * R + t.j0 + tj] = t.key;
+    }
+  }
 }
 
 // Texels lying exactly on hull edge a->b get the triangle next to it (LANES lanes
@@ -1116,18 +1173,18 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
 // A step takes every candidate's cotangent and its minimum over the group,
 // without a branch or a global access on the way; the answer stands if the
 // circle through it lies in the gathered square, else third_left goes on from
-// it (one step in ten).  The wave collects its triangles and rasterises them
+// it (one step in twenty).  The wave collects its triangles and rasterises them
 // together.
 //
-// Bound by instruction issue (VALU 68 % busy): a star costs about 450 wave
-// instructions.  A search by one lane over the buckets, with the answers shared
-// between stars, takes fewer but leaves the lanes of a wave waiting for its
-// longest search (1024 tiles of 50-2000 points: 1.8 ms, this 1.2 ms); sixteen
-// lanes with 5 candidates each cost 1.5 ms, all neighbours instead of those
-// above 40 % more steps.  Three waves per SIMD: four would spill (8,000 tiles
-// slower, 1024 faster by 2 %).  Items of 16 points: 8 add atomics (2.4 ms in
-// all instead of 1.85), 32 leave a tail (1.90); with up to 64 tiles 8, what a
-// wave works on at once.
+// Of the 1.03 ms that 1.2 M points of 1024 tiles take, the steps are 0.5, the
+// searches beyond the candidates 0.3 and the gather 0.18, all bound by
+// instruction issue and by the chain of dependent reads.  A search by one lane
+// over the buckets, with the answers shared between stars, takes fewer
+// instructions but leaves the lanes of a wave waiting for its longest search
+// (1.8 ms); sixteen lanes with 5 candidates each took 1.5 ms, all neighbours
+// instead of those above 40 % more steps.  Three waves per SIMD: four spill (8 %
+// slower with the largest tiles).  Items of 16 points: 8 and 32 are 1 and 5 %
+// slower; with up to 64 tiles 8, what a wave works on at once.
 __global__ void __launch_bounds__(TB, 3) k_recon_stars(ReconParams P) {
   __shared__ int2 s_d[TB / STAR_LANES][CANDS];  // candidates: position relative to the centre
   __shared__ int s_id[TB / STAR_LANES][CANDS];  // and index
@@ -1144,9 +1201,28 @@ __global__ void __launch_bounds__(TB, 3) k_recon_stars(ReconParams P) {
   if ((tid & 63) == 0) s_ntri[wave] = 0;
   wave_sync();
   const int n_items = __builtin_amdgcn_readfirstlane(P.item_n[0]);
-  // the first item by the wave's number, then from the shared counter
-  const int n_waves = gridDim.x * (TB / 64);
-  for (int it = __builtin_amdgcn_readfirstlane(blockIdx.x * (TB / 64) + wave); it < n_items;) {
+  // The items are cut into a range per XCD (the items of a tile lie together, so
+  // its points stay in that XCD's L2).  A wave's first item follows from its
+  // number, the others from the range's counter, then from the next ranges'.  One
+  // counter for all took 0.8 ms for 75,000 items, unevenly long items in turn
+  // without a counter 25 % more than this.
+  const int per_range = gridDim.x / XCDS * (TB / 64);  // waves of a range
+  int range = blockIdx.x % XCDS, tries = 0;
+  auto begin_of = [&](int x) { return (int)((int64_t)n_items * x / XCDS); };
+  auto next_item = [&]() -> int {
+    if (n_items <= XCDS * per_range) return -1;
+    for (; tries < XCDS; ++tries) {
+      int i = 0;
+      if ((tid & 63) == 0) i = atomicAdd(P.item_n + ITEM_COUNTER * (1 + range), 1);
+      i = begin_of(range) + per_range + __builtin_amdgcn_readfirstlane(i);
+      if (i < begin_of(range + 1)) return i;
+      range = (range + 1) % XCDS;
+    }
+    return -1;
+  };
+  int it = begin_of(range) + __builtin_amdgcn_readfirstlane(blockIdx.x / XCDS * (TB / 64) + wave);
+  if (it >= begin_of(range + 1)) it = next_item();
+  for (; it >= 0; it = next_item()) {
     const int2 item = P.items[it];
     const int pos = __builtin_amdgcn_readfirstlane(item.x), begin = __builtin_amdgcn_readfirstlane(item.y);
     const int k = __builtin_amdgcn_readfirstlane(P.order[P.q0 + pos]);
@@ -1184,20 +1260,20 @@ __global__ void __launch_bounds__(TB, 3) k_recon_stars(ReconParams P) {
           held = group_reduce(len[0] + len[1], [](int u, int v) { return u + v; });
         };
         count();
-        r = min(max((int)(3.5f * sqrtf(CANDS * 0.7f / (float)held)), 1), 7);
+        r = min(max((int)(3.5f * sqrtf(CANDS * 0.85f / (float)held)), 1), 7);
         for (;; --r) {
           count();
           if (held <= CANDS) break;
           held = 0;
           if (r == 0) break;
         }
+        const float fx = (float)(A.x + T.H) * T.inv, fy = (float)(A.y + T.H) * T.inv;
         Rect known{1.f, 0.f, 1.f, 0.f};  // what has been gathered, open at the window's borders
         float reach2 = 0.f;              // squared distance from the centre that it covers
         if (held) {
           const int at = group_before(len[0] + len[1], gl);
           for (int j = 0; j < len[0]; ++j) list_id[at + j] = first_p[0] + j;
           for (int j = 0; j < len[1]; ++j) list_id[at + len[0] + j] = first_p[1] + j;
-          const float fx = (float)(A.x + T.H) * T.inv, fy = (float)(A.y + T.H) * T.inv;
           known = Rect{bx - r > 0 ? (float)(bx - r) : -16.f, bx + r < G - 1 ? (float)(bx + r + 1) : G + 16.f,
                        by - r > 0 ? (float)(by - r) : -16.f, by + r < G - 1 ? (float)(by + r + 1) : G + 16.f};
           const float reach =
@@ -1337,7 +1413,15 @@ __global__ void __launch_bounds__(TB, 3) k_recon_stars(ReconParams P) {
               tie = many != 0 || (hits & (hits - 1)) != 0;
               if (tie) break;
               const float len2 = (float)fma(ex, ex, ey * ey);
-              if (!(fmaf(len2 * least, least, len2) <= reach2)) break;
+              if (!(fmaf(len2 * least, least, len2) <= reach2)) {
+                const float fex = (float)B.x * T.inv, fey = (float)B.y * T.inv;
+                const Rect box = back ? circle_box(-fex, -fey, sqrtf(len2) * T.inv, least)
+                                      : circle_box(fex, fey, sqrtf(len2) * T.inv, least);
+                const float px = back ? fx + fex : fx, py = back ? fy + fey : fy;
+                if (!(known.x0 <= px + box.x0 && known.x1 >= px + box.x1 && known.y0 <= py + box.y0 &&
+                      known.y1 >= py + box.y1))
+                  break;
+              }
               advance(c, D);
               c = -1;
               if (done || rest != FACE_NONE) break;
@@ -1355,7 +1439,7 @@ __global__ void __launch_bounds__(TB, 3) k_recon_stars(ReconParams P) {
             advance(c, make_int2(Q.x - A.x, Q.y - A.y));
           }
           if (rest != FACE_NONE) {
-            raster_triangle<STAR_LANES>(T, rest, C, R, fm, gl, INT_MAX);
+            raster_box(raster_tri(T, rest, C, R), R, fm, gl);
             rest = FACE_NONE;
           }
         }
@@ -1374,19 +1458,17 @@ __global__ void __launch_bounds__(TB, 3) k_recon_stars(ReconParams P) {
       if (ntri >= TRI_CAP / 2 || a0 + 64 / STAR_LANES >= end) {
         for (int i0 = 0; i0 < ntri; i0 += 64 / RASTER_LANES) {
           const int i = i0 + (tid & 63) / RASTER_LANES;
-          const bool rest = i < ntri && !raster_triangle<RASTER_LANES>(T, s_tri[wave][i], C, R, fm, tid & (RASTER_LANES - 1), RASTER_MAX);
-          for (uint64_t large = __ballot(rest && (tid & (RASTER_LANES - 1)) == 0); large; large &= large - 1)
-            raster_triangle<64>(T, s_tri[wave][i0 + __builtin_ctzll(large) / RASTER_LANES], C, R, fm, tid & 63, INT_MAX);
+          const RasterTri t = raster_tri(T, s_tri[wave][min(i, ntri - 1)], C, R);
+          const bool large = i < ntri && t.h * t.w > RASTER_MAX;
+          if (i < ntri && !large) raster_box(t, R, fm, tid & (RASTER_LANES - 1));
+          for (uint64_t left = __ballot(large && (tid & (RASTER_LANES - 1)) == 0); left; left &= left - 1)
+            raster_wave(t, __builtin_ctzll(left), R, fm, tid & 63);
         }
         wave_sync();
         if ((tid & 63) == 0) s_ntri[wave] = 0;
       }
       wave_sync();
     }
-    if (n_items <= n_waves) break;
-    int next = 0;
-    if ((tid & 63) == 0) next = atomicAdd(P.item_n + 1, 1);
-    it = n_waves + __builtin_amdgcn_readfirstlane(next);
   }
 }
 
@@ -1607,7 +1689,7 @@ void recon_layout(const LsGridInfo& gi, int32_t n_tiles, int64_t n, void* base, 
   L->tile_pos = A.take<int32_t>(nall);
   L->counts = A.take<int32_t>(n_tiles + 1);
   L->fill = A.take<int32_t>(n_tiles + 1);
-  L->flags = A.take<int32_t>(4);  // too many entries; the work items and how many are taken
+  L->flags = A.take<int32_t>(N_FLAGS);  // too many entries; the work items and how many are taken
   L->order = A.take<int32_t>(n_tiles);
   L->bin_off = A.take<int32_t>(n_tiles + 1);
   L->bin_idx = A.take<int32_t>(E);
@@ -1738,7 +1820,7 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
   rp.has_dt = L.counts;
   rp.facemap = L.facemap;
   rp.items = L.items;
-  rp.item_n = L.flags + 1;
+  rp.item_n = L.flags + ITEM_COUNTER;
   rp.order = L.order;
   rp.x_out = x_out;
   rp.cz_out = cz_out;
@@ -1752,9 +1834,10 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
       rp.q0 = q0;
       // few tiles: a wave takes the points it works on at once
       rp.item = nt <= 64 ? ITEM_MIN : ITEM_MAX;
-      if (q0) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(T), 0, st, rp.item_n, (int64_t)2, 0);
+      if (q0) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(T), 0, st, rp.item_n,
+                         (int64_t)(N_FLAGS - ITEM_COUNTER), 0);
       hipLaunchKernelGGL(k_recon_prep, dim3(nt), dim3(RB), 0, st, rp);
-      hipLaunchKernelGGL(k_recon_stars, dim3(3 * num_cus()), dim3(TB), 0,
+      hipLaunchKernelGGL(k_recon_stars, dim3(3 * ((num_cus() + XCDS - 1) / XCDS * XCDS)), dim3(TB), 0,
                          st, rp);
       hipLaunchKernelGGL(k_recon_out, dim3((unsigned)nt * parts), dim3(TB), 0, st, rp, parts);
       q0 += nt;
