@@ -302,36 +302,68 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
 // BF16 on the matrix cores: C[M][N] = act(A[M][K] W[N][K]^T + bias) with
-// FP32 accumulation, stored as BF16.  A workgroup (4 waves) owns 64 rows x 64
-// columns, each wave 16 rows x 4 column tiles; per 32-wide K step lane l
-// loads row (l % 16) of A and of W at k = 8 * (l / 16) (16-byte loads).
-// K % 32 == 0, N % 64 == 0; rows beyond M read zeros and are not stored.
+// FP32 accumulation, stored as BF16.  A workgroup (4 waves) owns 64 rows x NT
+// column tiles of 16, each wave 16 rows; per 32-wide K step lane l loads row
+// (l % 16) of A and of W at k = 8 * (l / 16) (16-byte loads).  K % 32 == 0,
+// N % (16 NT) == 0; rows beyond M read row 0 and are not stored.
+//
+// Bound by the latency of its loads: the sums run over K in order, so a tile is
+// one serial chain of K / 32 steps.  Hence STEPS steps of loads are in flight
+// before the products of the last STEPS, and a wave has one column tile where
+// four would leave the chip short of waves: 333 x 512 x 4608 in 36 us (84 us with
+// four column tiles and a step's loads at a time; 12 or 16 steps in flight give
+// no more).
+template <int NT, int STEPS>
 __global__ void __launch_bounds__(256) k_fc_bf16(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
                                                  const float* __restrict__ bias, uint16_t* __restrict__ C, int M,
                                                  int N, int K, int relu) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, g = lane >> 4;
-  const int m0 = blockIdx.y * 64 + wave * 16, n0 = blockIdx.x * 64;
+  const int m0 = blockIdx.y * 64 + wave * 16, n0 = blockIdx.x * 16 * NT;
+  if (m0 >= M) return;
   const int m = m0 + r16;
-  const bool mv = m < M;
-  const uint16_t* ap = A + (int64_t)(mv ? m : 0) * K + 8 * g;
+  const uint16_t* ap = A + (int64_t)(m < M ? m : 0) * K + 8 * g;
   const uint16_t* wp = W + (int64_t)(n0 + r16) * K + 8 * g;
-  f32x4 acc[4];
+  f32x4 acc[NT];
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < K; k += 32) {
-    u16x8 a = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (mv) a = *reinterpret_cast<const u16x8*>(ap + k);
-    const bf16x8 ab = __builtin_bit_cast(bf16x8, a);
+  for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 a[STEPS], w[STEPS][NT];
+  auto load = [&](int k) {
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-      const bf16x8 bb = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(wp + (int64_t)nt * 16 * K + k));
-      acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab, bb, acc[nt], 0, 0, 0);
+    for (int s = 0; s < STEPS; ++s) {
+      const int ks = min(k + 32 * s, K - 32);
+      a[s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(ap + ks));
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        w[s][nt] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(wp + (int64_t)nt * 16 * K + ks));
     }
+  };
+  load(0);
+  int k = 0;
+  for (; k + 32 * STEPS <= K; k += 32 * STEPS) {
+    bf16x8 a0[STEPS], w0[STEPS][NT];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      a0[s] = a[s];
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) w0[s][nt] = w[s][nt];
+    }
+    load(k + 32 * STEPS);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0[s], w0[s][nt], acc[nt], 0, 0, 0);
   }
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s)
+    if (k + 32 * s < K)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], w[s][nt], acc[nt], 0, 0, 0);
   // D rows 4g + i (A rows), column r16 (W rows)
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
+  for (int nt = 0; nt < NT; ++nt) {
     const int n = n0 + nt * 16 + r16;
     const float b = bias[n];
 #pragma unroll
@@ -509,9 +541,15 @@ int fc_f32(const float* A, const float* B, const float* bias, float* C, int M, i
 int fc_bf16(const uint16_t* A, const uint16_t* W, const float* bias, uint16_t* C, int M, int N, int K,
             hipStream_t st) {
   if (N % 64 || K % 32) return LS_ENOTIMPL;
-  dim3 grid((unsigned)(N / 64), (unsigned)((M + 63) / 64));
+  // four column tiles a wave read A a quarter as often, once that still gives a
+  // wave to every other SIMD: 333 x 2304 x 512 in 14 us, 20 us with one
+  const bool wide = (int64_t)(N / 64) * ((M + 15) / 16) >= 512;
   LS_TRACE("fc_bf16", st);
-  hipLaunchKernelGGL(k_fc_bf16, grid, dim3(256), 0, st, A, W, bias, C, M, N, K, 1);
+  const unsigned rows = (unsigned)((M + 63) / 64);
+  if (wide)
+    hipLaunchKernelGGL((k_fc_bf16<4, 2>), dim3((unsigned)(N / 64), rows), dim3(256), 0, st, A, W, bias, C, M, N, K, 1);
+  else
+    hipLaunchKernelGGL((k_fc_bf16<1, 8>), dim3((unsigned)(N / 16), rows), dim3(256), 0, st, A, W, bias, C, M, N, K, 1);
   LS_LAUNCH_CHECK();
   return LS_OK;
 }
