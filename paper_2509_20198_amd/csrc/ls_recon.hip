@@ -47,6 +47,7 @@ namespace {
 
 constexpr int RB = 512;                  // threads of a preparation workgroup
 constexpr int PREP_INTS = 12000;         // its LDS: windows up to about 3,000 points sort there
+constexpr int PREP_BATCH = 4;            // points a lane reads at a time
 constexpr int MAXG = 76;                 // max buckets per side
 constexpr int MAXB = MAXG * MAXG;        // max buckets
 static_assert(2 * (MAXB + 1) <= PREP_INTS, "bucket offsets must fit twice in the preparation's LDS");
@@ -1018,6 +1019,10 @@ __device__ __forceinline__ void write_zero_tile(const ReconParams& P, int k) {
 }
 
 // Phases a-b, one workgroup per tile: gather, bucket sort, canonical points.
+// Bound by the chains of dependent reads (entry, point, attributes) of a tile's
+// 512 lanes, so each pass over the points reads PREP_BATCH of them at a time, and
+// attributes follow in a pass of their own instead of bucket by bucket: a window
+// of 7,000 points 148 -> 123 us (and 1024 tiles of 50-2000 points 116 -> 100).
 __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
   // the raw bucket offsets at the start, the canonical ones at the end, and
   // between them the sort keys and entries of a window that fits
@@ -1053,13 +1058,25 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
   // ---- a. gather + bucket histogram
   for (int b = tid; b <= NB; b += RB) s_b[b] = 0;
   __syncthreads();
-  for (int e = tid; e < cnt; e += RB) {
-    const int32_t gi = P.bin_idx[off + e];
-    const int u = (int)((int64_t)P.x[gi] - cx), v = (int)((int64_t)P.y[gi] - cy);
-    P.su[off + e] = u;
-    P.sv[off + e] = v;
-    const int b = bucket_1d(v + H, G, W2) * G + bucket_1d(u + H, G, W2);
-    P.sslot[off + e] = atomicAdd(&s_b[b], 1);
+  for (int e0 = tid; e0 < cnt; e0 += PREP_BATCH * RB) {
+    int32_t gi[PREP_BATCH], x[PREP_BATCH], y[PREP_BATCH];
+#pragma unroll
+    for (int j = 0; j < PREP_BATCH; ++j) gi[j] = P.bin_idx[off + min(e0 + j * RB, cnt - 1)];
+#pragma unroll
+    for (int j = 0; j < PREP_BATCH; ++j) {
+      x[j] = P.x[gi[j]];
+      y[j] = P.y[gi[j]];
+    }
+#pragma unroll
+    for (int j = 0; j < PREP_BATCH; ++j) {
+      const int e = e0 + j * RB;
+      if (e >= cnt) break;
+      const int u = (int)((int64_t)x[j] - cx), v = (int)((int64_t)y[j] - cy);
+      P.su[off + e] = u;
+      P.sv[off + e] = v;
+      const int b = bucket_1d(v + H, G, W2) * G + bucket_1d(u + H, G, W2);
+      P.sslot[off + e] = atomicAdd(&s_b[b], 1);
+    }
   }
   __syncthreads();
   block_scan_excl(s_b, NB + 1, s_tmp);
@@ -1080,12 +1097,24 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
     return rank_of(e0) > rank_of(e1);
   };
   auto bucket_sort = [&](uint64_t* __restrict__ key, int* __restrict__ idx) -> int {
-    for (int e = tid; e < cnt; e += RB) {
-      const int u = P.su[off + e], v = P.sv[off + e];
-      const int b = bucket_1d(v + H, G, W2) * G + bucket_1d(u + H, G, W2);
-      const int pos = s_b[b] + P.sslot[off + e];
-      key[pos] = key_of(u, v);
-      idx[pos] = e;
+    for (int e0 = tid; e0 < cnt; e0 += PREP_BATCH * RB) {
+      int u[PREP_BATCH], v[PREP_BATCH], slot[PREP_BATCH];
+#pragma unroll
+      for (int j = 0; j < PREP_BATCH; ++j) {
+        const int e = min(e0 + j * RB, cnt - 1);
+        u[j] = P.su[off + e];
+        v[j] = P.sv[off + e];
+        slot[j] = P.sslot[off + e];
+      }
+#pragma unroll
+      for (int j = 0; j < PREP_BATCH; ++j) {
+        const int e = e0 + j * RB;
+        if (e >= cnt) break;
+        const int b = bucket_1d(v[j] + H, G, W2) * G + bucket_1d(u[j] + H, G, W2);
+        const int pos = s_b[b] + slot[j];
+        key[pos] = key_of(u[j], v[j]);
+        idx[pos] = e;
+      }
     }
     __syncthreads();
     // ---- b. per-bucket sort + dedupe
@@ -1117,11 +1146,26 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
         if (i == lo || key[i] != key[i - 1]) {
           const uint64_t kk = key[i];
           P.cuv[w] = make_int2((int)(uint32_t)kk - (1 << 20), (int)(uint32_t)(kk >> 32) - (1 << 20));
-          const int32_t gi = P.bin_idx[off + idx[i]];
-          const uint16_t* c3 = P.rgb + 3 * (int64_t)gi;
-          P.cattr[w] = make_int4(P.z[gi], c3[0], c3[1], c3[2]);
+          P.sslot[w] = idx[i];  // the slots have been used
           ++w;
         }
+    }
+    __syncthreads();
+    for (int w0 = tid; w0 < mm; w0 += PREP_BATCH * RB) {
+      int32_t gi[PREP_BATCH];
+      int4 at[PREP_BATCH];
+#pragma unroll
+      for (int j = 0; j < PREP_BATCH; ++j) gi[j] = P.sslot[off + min(w0 + j * RB, mm - 1)];
+#pragma unroll
+      for (int j = 0; j < PREP_BATCH; ++j) gi[j] = P.bin_idx[off + gi[j]];
+#pragma unroll
+      for (int j = 0; j < PREP_BATCH; ++j) {
+        const uint16_t* c3 = P.rgb + 3 * (int64_t)gi[j];
+        at[j] = make_int4(P.z[gi[j]], c3[0], c3[1], c3[2]);
+      }
+#pragma unroll
+      for (int j = 0; j < PREP_BATCH; ++j)
+        if (w0 + j * RB < mm) P.cattr[off + w0 + j * RB] = at[j];
     }
     return mm;
   };
