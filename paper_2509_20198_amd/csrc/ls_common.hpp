@@ -44,6 +44,22 @@ static inline hipStream_t ls_stream(void* s) { return reinterpret_cast<hipStream
 
 static inline size_t ls_align(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
+// Values of other lanes of the sixteen of a row (DPP control CTRL).
+template <int CTRL>
+__device__ __forceinline__ int row_move(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float row_move(float v) {
+  return __builtin_bit_cast(float, row_move<CTRL>(__builtin_bit_cast(int, v)));
+}
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+  const uint64_t w = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)row_move<CTRL>((int)(uint32_t)w), hi = (uint32_t)row_move<CTRL>((int)(uint32_t)(w >> 32));
+  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
 // Bump allocator over the caller's workspace.
 struct LsArena {
   char* base;

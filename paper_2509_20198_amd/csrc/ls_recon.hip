@@ -457,20 +457,6 @@ __device__ __forceinline__ int incircle_sos(int a, int b, int c, int d, int2 pa,
 
 // ---- stars: a group of eight lanes works on one star
 constexpr int STAR_LANES = 8;  // as many as RASTER_LANES
-template <int CTRL>
-__device__ __forceinline__ int row_move(int v) {
-  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
-}
-template <int CTRL>
-__device__ __forceinline__ float row_move(float v) {
-  return __builtin_bit_cast(float, row_move<CTRL>(__builtin_bit_cast(int, v)));
-}
-template <int CTRL>
-__device__ __forceinline__ double row_move(double v) {
-  const uint64_t w = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)row_move<CTRL>((int)(uint32_t)w), hi = (uint32_t)row_move<CTRL>((int)(uint32_t)(w >> 32));
-  return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
-}
 // f over the group: the other lane of a pair, the other pair of a quad, the
 // other quad.
 template <class V, class F>

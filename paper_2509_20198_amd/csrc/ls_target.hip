@@ -54,6 +54,16 @@ struct Run {
   uint32_t r, g, b, n;
 };
 
+// u added to that of the lane CTRL names.
+template <int CTRL>
+__device__ __forceinline__ void add_lane(Run& u) {
+  u.z += (long long)(((uint64_t)(uint32_t)row_move<CTRL>((int)(u.z >> 32)) << 32) | (uint32_t)row_move<CTRL>((int)u.z));
+  u.r += (uint32_t)row_move<CTRL>((int)u.r);
+  u.g += (uint32_t)row_move<CTRL>((int)u.g);
+  u.b += (uint32_t)row_move<CTRL>((int)u.b);
+  u.n += (uint32_t)row_move<CTRL>((int)u.n);
+}
+
 __global__ void __launch_bounds__(PT_THREADS) k_splat_mean(MeanParams p) {
   __shared__ unsigned long long s_z[MEAN_WIN];
   __shared__ uint32_t s_c[MEAN_WIN][4];  // R, G, B sums and count
@@ -134,7 +144,28 @@ __global__ void __launch_bounds__(PT_THREADS) k_splat_mean(MeanParams p) {
       u.b += point_colour(r, s, 2);
       u.n += 1;
     }
-    if (u.n) flush(cur, u);
+    // Lanes that end on the same texel add their sums in registers first, the
+    // sixteen of a row or the four of a quad: the LDS adds of many lanes to one
+    // address run one after the other (16 tiles of 2 M points, 490 to a texel:
+    // 192 -> 162 us; at six points a texel few quads agree, and it costs nothing).
+    bool add = u.n != 0;
+    if (window) {
+      const int w = add ? (int)((uint32_t)cur - lo) : -1;
+      const int lane = tid & 63;
+      const int w16 = row_move<0x150>(w), w4 = row_move<0x00>(w);  // the first lane's
+      const uint64_t same16 = __ballot(w == w16 && w >= 0), same4 = __ballot(w == w4 && w >= 0);
+      if (((same4 >> (lane & 60)) & 0xF) == 0xF) {
+        add_lane<0xB1>(u);
+        add_lane<0x4E>(u);
+        add = (lane & 3) == 0;
+        if (((same16 >> (lane & 48)) & 0xFFFF) == 0xFFFF) {
+          add_lane<0x124>(u);  // four and eight lanes on
+          add_lane<0x128>(u);
+          add = (lane & 15) == 0;
+        }
+      }
+    }
+    if (add) flush(cur, u);
     if (window) {
       __syncthreads();
       // one lane per (texel, field): the lanes of one atomic instruction
