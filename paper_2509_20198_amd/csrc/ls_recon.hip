@@ -35,9 +35,9 @@
 // Three launches rather than one workgroup per tile from end to end: the work
 // of a tile follows its point count (20 to tens of thousands), and a launch
 // over runs of points spreads the largest tile over the chip.  One tile of 400
-// points 542 -> 194 us (reconstruction and network), one of 16,000 points
-// 16.3 -> 0.78 ms, 1024 tiles of 50-2000 points 2.22 -> 1.54 ms, 16384 tiles of
-// 20-5000 points 12.5 -> 7.9 ms.
+// points 536 -> 190 us (reconstruction and network), one of 16,000 points
+// 16.3 -> 0.78 ms, 1024 tiles of 50-2000 points 2.22 -> 1.51 ms, 16384 tiles of
+// 20-5000 points 13.2 -> 7.7 ms.
 #include <algorithm>
 #include <mutex>
 
@@ -1206,8 +1206,8 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
 // it (one step in twenty).  The wave collects its triangles and rasterises them
 // together.
 //
-// Of the 1.03 ms that 1.2 M points of 1024 tiles take, the steps are 0.5, the
-// searches beyond the candidates 0.3 and the gather 0.18, all bound by
+// Of the 1.15 ms that 1.2 M points of 1024 tiles take, the steps are 0.5, the
+// searches beyond the candidates 0.35 and the gather 0.18, all bound by
 // instruction issue and by the chain of dependent reads.  A search by one lane
 // over the buckets, with the answers shared between stars, takes fewer
 // instructions but leaves the lanes of a wave waiting for its longest search
