@@ -23,6 +23,10 @@
 // saved: 20 against 11 cycles of LDS per product.)  The weights are packed
 // in the order of use and read from global memory (L2), one block ahead.
 //
+// Taps outside the plane are zeros that are multiplied like the others.  With
+// an infinite weight that gives NaN where the tap should count for nothing, so
+// sums that come out NaN next to the border are taken again without these taps.
+//
 // Bound: the matrix cores for the layers with 32 and more channels, the
 // exposed staging for the others.  Whole forward, 99 tiles of 96 x 96: 0.60
 // ms (75 TFLOP/s), one tile 0.14 ms; with the vector kernel this replaced (a
@@ -62,10 +66,50 @@ struct ConvGeom {
   int tiles_x, tiles_y;    // workgroup tiles of one image
   int ntiles;              // of the batch
   int chunk;               // tiles per XCD
+  int in_y0, in_y1, in_x0, in_x1;  // pixels that the tensors of both parts hold
 };
 
+// The sums of a wave that are NaN, of pixels next to the border, in the order of
+// the products: without the taps outside the plane or outside a part's tensor.
+// px: the lane's staged pixel at tap (0, 0) of its first pixel tile.
+template <int KB, int NT>
+__device__ __forceinline__ void sums_within(const ConvArgs& A, const ConvGeom& G, f32x4 (&acc)[NT], const float* px,
+                                            int PW, int SP, int mw, int g, int oy, int ox) {
+  constexpr int V = KB / 4;
+  const int ca = A.src.a.c, cin = ca + A.src.b.c, co = mw * 16 + 4 * g, x = A.x0 + ox;
+  auto holds = [&](const SrcPart& p, int yy, int xx) {
+    const int sy = p.up ? yy >> 1 : yy - p.oy, sx = p.up ? xx >> 1 : xx - p.ox;
+    return yy >= 0 && xx >= 0 && yy < A.H && xx < A.W && sy >= 0 && sx >= 0 && sy < p.h && sx < p.w;
+  };
+#pragma unroll 1
+  for (int e = 0; e < 4 * NT; ++e, px += e & 3 ? 0 : 2 * PW * SP, oy += e & 3 ? 0 : 2) {
+    float v = 0.f;
+#pragma unroll
+    for (int k = 0; k < 4 * NT; ++k) v = k == e ? acc[k >> 2][k & 3] : v;
+    const int y = A.y0 + oy;
+    if (v == v || co >= A.cout || oy >= A.Ho || ox >= A.Wo ||
+        (y > G.in_y0 && y + 1 < G.in_y1 && x > G.in_x0 && x + 1 < G.in_x1))
+      continue;
+    float s = A.bias ? A.bias[co + (e & 3)] : 0.f;
+#pragma unroll 1
+    for (int tap = 0; tap < 9; ++tap) {
+      const int ky = tap / 3, kx = tap - 3 * ky;
+      const bool in_a = holds(A.src.a, y + ky - 1, x + kx - 1), in_b = holds(A.src.b, y + ky - 1, x + kx - 1);
+      const float* wt = A.wt + (int64_t)(mw * 9 + tap) * cin * 16 + (4 * g + (e & 3)) * V;
+#pragma unroll 1
+      for (int ci = 0; ci < cin; ++ci)
+        if (ci < ca ? in_a : in_b)
+          s = fmaf(px[(ky * PW + kx) * SP + ci], wt[((ci / KB) * 64 + (ci & 3) * 16) * V + ((ci % KB) >> 2)], s);
+    }
+#pragma unroll
+    for (int k = 0; k < 4 * NT; ++k) acc[k >> 2][k & 3] = k == e ? s : acc[k >> 2][k & 3];
+  }
+}
+
+// At most 96 scalar registers: eight waves per SIMD also with the code for sums
+// that are NaN (which never runs otherwise; without the bound 2 % slower).
 template <int KB, int NT, bool MASK>
-__global__ void __launch_bounds__(512) k_conv_f32_mfma(ConvArgs A, ConvGeom G) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_num_sgpr(96))) k_conv_f32_mfma(ConvArgs A, ConvGeom G) {
   constexpr int V = KB / 4;
   typedef typename VecOf<V>::T vec;
   extern __shared__ __align__(16) float s_in[];
@@ -186,6 +230,19 @@ __global__ void __launch_bounds__(512) k_conv_f32_mfma(ConvArgs A, ConvGeom G) {
 #pragma unroll
       for (int s = 0; s < V; ++s) bf[nt][s] = bn[nt][s];
   }
+  // ---- sums that zeros outside the plane have made NaN, once more without them
+  const int by = A.y0 + oy0, bx = A.x0 + ox0;  // the workgroup's first pixel
+  if (by <= G.in_y0 || bx <= G.in_x0 || by + 2 * NT * G.wy >= G.in_y1 || bx + 8 * G.wx >= G.in_x1) {
+    // NaN if one of the sums is, or if they hold infinities of both signs
+    f32x4 any = acc[0];
+#pragma unroll
+    for (int nt = 1; nt < NT; ++nt) any += acc[nt];
+    const float t = any[0] + any[1] + any[2] + any[3];
+    if (__ballot(t != t)) {
+      const int oy = wyi * 2 * NT + (r16 >> 3), ox = wxi * 8 + (r16 & 7);
+      sums_within<KB, NT>(A, G, acc, s_in + (oy * PW + ox) * SP, PW, SP, mw, g, oy0 + oy, ox0 + ox);
+    }
+  }
   // ---- epilogue: lane = 4 consecutive channels of one pixel per tile
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
@@ -245,6 +302,16 @@ ConvPlan conv_plan(const ConvArgs& a) {
   const int64_t tiles = (int64_t)a.B * p.g.tiles_x * p.g.tiles_y;
   p.g.ntiles = (int)std::min<int64_t>(tiles, 0x7fffffff);
   p.g.chunk = (int)((p.g.ntiles + 7LL) / 8);
+  p.g.in_y0 = p.g.in_x0 = 0;
+  p.g.in_y1 = a.H;
+  p.g.in_x1 = a.W;
+  for (const SrcPart* q : {&a.src.a, &a.src.b}) {
+    if (!q->c) continue;
+    p.g.in_y0 = std::max(p.g.in_y0, q->up ? 0 : q->oy);
+    p.g.in_x0 = std::max(p.g.in_x0, q->up ? 0 : q->ox);
+    p.g.in_y1 = std::min(p.g.in_y1, q->up ? 2 * q->h : q->oy + q->h);
+    p.g.in_x1 = std::min(p.g.in_x1, q->up ? 2 * q->w : q->ox + q->w);
+  }
   return p;
 }
 
