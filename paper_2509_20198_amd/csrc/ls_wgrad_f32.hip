@@ -46,7 +46,7 @@ __global__ void __launch_bounds__(WT) k_wgrad_f32_mfma(WgradArgs A, WgradGeom G)
   __shared__ __align__(16) float s_mem[TILE_PX * GP + PATCH_PX * CB];
   float* s_g = s_mem;
   float* s_x = s_mem + TILE_PX * GP;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, g = lane >> 4;
   const int cin = A.src.a.c + A.src.b.c;
   const int cib = blockIdx.y % G.ncib, co0 = (blockIdx.y / G.ncib) * GP;
@@ -54,7 +54,7 @@ __global__ void __launch_bounds__(WT) k_wgrad_f32_mfma(WgradArgs A, WgradGeom G)
   const bool bias = cib == 0;
   const SrcPart S = c0 < A.src.a.c ? A.src.a : A.src.b;  // the block lies in one part
   const int sc = S.coff + (c0 < A.src.a.c ? c0 : c0 - A.src.a.c);
-  const int PW = G.tw + 2, tw4 = G.tw >> 2, npx = G.tw * G.th, npatch = PW * (G.th + 2);
+  const int PW = G.tw + 2, npx = G.tw * G.th, npatch = PW * (G.th + 2);
   // staged offset of the lane's column in column tile t
   int off[NTL];
 #pragma unroll
@@ -109,21 +109,25 @@ __global__ void __launch_bounds__(WT) k_wgrad_f32_mfma(WgradArgs A, WgradGeom G)
         reinterpret_cast<float4*>(s_x)[e] = make_float4(k ? v.x : 0.f, k ? v.y : 0.f, k ? v.z : 0.f, k ? v.w : 0.f);
     }
     __syncthreads();
-    int row = wave / tw4, c = wave - row * tw4;  // group of four pixels: 4 c .. 4 c + 3 of a row
-    for (int s = wave; s < tw4 * G.th; s += 4) {
+    // groups of four pixels (4 c .. 4 c + 3 of a row) inside the window: a padding
+    // pixel's gradient is zero, but its products with infinite inputs are not
+    const int vw = min(G.tw, A.Wo - tx0), w4 = (vw + 3) >> 2, ngrp = w4 * min(G.th, A.Ho - ty0);
+    int row = 0, c = wave;
+    for (; c >= w4; c -= w4) ++row;
+    for (int s = wave; s < ngrp; s += 4) {
       const float af = s_g[(row * G.tw + 4 * c + g) * GP + r16];
       const float* xa = s_x + (row * PW + 4 * c + g) * CB;
       float bf[NTL];
 #pragma unroll
       for (int t = 0; t < NTL; ++t) bf[t] = xa[off[t]];
+      if (4 * c + 4 > vw) {  // the last group of a row
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) bf[t] = 4 * c + g < vw ? bf[t] : 0.f;
+      }
 #pragma unroll
       for (int t = 0; t < NTL; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(af, bf[t], acc[t], 0, 0, 0);
       if (bias) acc[NTL] = __builtin_amdgcn_mfma_f32_16x16x4f32(af, 1.f, acc[NTL], 0, 0, 0);
-      c += 4;
-      while (c >= tw4) {
-        c -= tw4;
-        ++row;
-      }
+      for (c += 4; c >= w4; c -= w4) ++row;
     }
     __syncthreads();  // every wave is done with the staged tile
   }

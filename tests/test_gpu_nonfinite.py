@@ -1,6 +1,7 @@
-"""FP32 network with infinite and NaN weights: only what a conv's taps reach is
-affected.  A tap outside the plane, or outside the tensor that a wider plane
-embeds, contributes nothing."""
+"""FP32 network with infinite weights and inputs: only what a conv's taps reach
+is affected.  A tap outside the plane, or outside the tensor that a wider plane
+embeds, contributes nothing; neither does an input outside the window that the
+head's weight gradient sums over."""
 import numpy as np
 import pytest
 import torch
@@ -57,3 +58,22 @@ def test_taps_outside_the_plane(res, pad, tap, value):
     finally:
         for p in (0, 1):
             ls.set_conv_config(10, ls.FP32, p, -1)
+
+
+@pytest.mark.parametrize("res,pad", [(20, 6), (22, 5), (4, 6)])
+def test_inputs_outside_the_heads_window(res, pad):
+    """Saved activations of finite inputs: the head's weight gradient does not
+    see inputs beyond the one-texel ring of its window."""
+    g, w, x, gy = _case(res, pad, 5)
+    R = g.R
+    wt, xt, gt = (torch.from_numpy(a).cuda() for a in (w, x, gy))
+    act = torch.empty(ls.act_bytes(g, 2, ls.FP32), dtype=torch.uint8, device="cuda")
+    ls.refine_tiles(wt, xt, None, g, ls.FP32, want_tex=False, act_save=act)
+    want, _ = ls.refine_backward(wt, xt, gt, g, ls.FP32, act_save=act)
+    far = torch.ones((R, R), dtype=torch.bool)
+    far[pad - 1:pad + res + 1, pad - 1:pad + res + 1] = False
+    xt[:, far.cuda()] = float("inf")
+    got, _ = ls.refine_backward(wt, xt, gt, g, ls.FP32, act_save=act)
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).all()
+    assert torch.equal(got[-HEAD:], want[-HEAD:])
