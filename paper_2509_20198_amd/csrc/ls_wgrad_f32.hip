@@ -10,7 +10,8 @@
 // taps.  Its four waves take every fourth group of four pixels, and their sums
 // are added in LDS in a fixed order, so the partial sums are deterministic.
 // Tiles are about 256 pixels, 8 to 32 wide, whichever pads the plane least
-// (24 x 8 on the 24-wide planes).
+// (24 x 8 on the 24-wide planes); several whole images one above the other where
+// a plane has at most 10 x 10 texels.
 //
 // Bound: at small batches the exposed staging of the one or two tiles a
 // workgroup gets, else the matrix cores (ten products per ten LDS reads).  24
@@ -32,12 +33,13 @@ constexpr int TILE_PX = 256;    // output pixels of a tile at most
 constexpr int PATCH_PX = 340;   // and its input patch: 10 x 34, 18 x 18, 26 x 10, 34 x 10
 
 struct WgradGeom {
-  int tw, th;              // tile, tw a multiple of 8
+  int tw, th;              // tile, tw a multiple of 4
   int tiles_x, ntiles, per_img;
+  int ni;                  // whole images of a tile, one above the other (PACK)
   int ncib;                // input-channel blocks
 };
 
-template <int CB>
+template <int CB, bool PACK>
 __global__ void __launch_bounds__(WT) k_wgrad_f32_mfma(WgradArgs A, WgradGeom G) {
   constexpr int NTL = CB == 16 ? 9 : 5;  // column tiles: a tap, or two taps of 8 channels
   constexpr int GP = 16;                 // output channels of a workgroup
@@ -54,7 +56,8 @@ __global__ void __launch_bounds__(WT) k_wgrad_f32_mfma(WgradArgs A, WgradGeom G)
   const bool bias = cib == 0;
   const SrcPart S = c0 < A.src.a.c ? A.src.a : A.src.b;  // the block lies in one part
   const int sc = S.coff + (c0 < A.src.a.c ? c0 : c0 - A.src.a.c);
-  const int PW = G.tw + 2, npx = G.tw * G.th, npatch = PW * (G.th + 2);
+  const int ni = PACK ? G.ni : 1;
+  const int PW = G.tw + 2, npx = G.tw * G.th * ni, npatch = PW * (G.th + 2) * ni;
   // staged offset of the lane's column in column tile t
   int off[NTL];
 #pragma unroll
@@ -66,28 +69,31 @@ __global__ void __launch_bounds__(WT) k_wgrad_f32_mfma(WgradArgs A, WgradGeom G)
 #pragma unroll
   for (int t = 0; t <= NTL; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int tile = blockIdx.x; tile < G.ntiles; tile += gridDim.x) {
-    const int b = tile / G.per_img, tt = tile - b * G.per_img;
+    const int b = PACK ? tile * G.ni : tile / G.per_img, tt = PACK ? 0 : tile - b * G.per_img;
     const int ty0 = (tt / G.tiles_x) * G.th, tx0 = (tt % G.tiles_x) * G.tw;
+    const int nb = PACK ? min(G.ni, A.B - b) : 1;  // images
     // every load of the tile before its LDS writes: one memory round trip
     float4 gv[NGI], gm[NGI], xv[NXI];
     bool gok[NGI], xok[NXI];
 #pragma unroll
     for (int i = 0; i < NGI; ++i) {
       const int e = tid + WT * i, px = e >> 2, q = e & 3;
-      const int r = px / G.tw, c = px - r * G.tw;
-      gok[i] = px < npx && ty0 + r < A.Ho && tx0 + c < A.Wo && co0 + 4 * q < A.cout;
-      const int64_t o = gok[i] ? (((int64_t)b * A.Ho + ty0 + r) * A.Wo + tx0 + c) * A.d_stride + co0 + 4 * q : 0;
+      const int vr = px / G.tw, c = px - vr * G.tw;
+      const int im = PACK ? vr / G.th : 0, r = vr - im * G.th;
+      gok[i] = px < npx && im < nb && ty0 + r < A.Ho && tx0 + c < A.Wo && co0 + 4 * q < A.cout;
+      const int64_t o = gok[i] ? (((int64_t)(b + im) * A.Ho + ty0 + r) * A.Wo + tx0 + c) * A.d_stride + co0 + 4 * q : 0;
       gv[i] = *reinterpret_cast<const float4*>(A.dA + o);
       if (A.mask) gm[i] = *reinterpret_cast<const float4*>(A.mask + o);
     }
 #pragma unroll
     for (int i = 0; i < NXI; ++i) {
       const int e = tid + WT * i, px = e / (CB / 4), q = e % (CB / 4);
-      const int r = px / PW, c = px - r * PW;
+      const int vr = px / PW, c = px - vr * PW;
+      const int im = PACK ? vr / (G.th + 2) : 0, r = vr - im * (G.th + 2);
       const int yy = A.y0 + ty0 + r - 1, xx = A.x0 + tx0 + c - 1;
       const int sy = S.up ? yy >> 1 : yy - S.oy, sx = S.up ? xx >> 1 : xx - S.ox;
-      xok[i] = px < npatch && yy >= 0 && xx >= 0 && yy < A.H && xx < A.W && sy >= 0 && sx >= 0 && sy < S.h && sx < S.w;
-      const int64_t o = (xok[i] ? (((int64_t)b * S.h + sy) * S.w + sx) * S.stride : 0) + sc + 4 * q;
+      xok[i] = px < npatch && im < nb && yy >= 0 && xx >= 0 && yy < A.H && xx < A.W && sy >= 0 && sx >= 0 && sy < S.h && sx < S.w;
+      const int64_t o = (xok[i] ? (((int64_t)(b + im) * S.h + sy) * S.w + sx) * S.stride : 0) + sc + 4 * q;
       xv[i] = *reinterpret_cast<const float4*>(S.f32 + o);
     }
 #pragma unroll
@@ -111,12 +117,12 @@ __global__ void __launch_bounds__(WT) k_wgrad_f32_mfma(WgradArgs A, WgradGeom G)
     __syncthreads();
     // groups of four pixels (4 c .. 4 c + 3 of a row) inside the window: a padding
     // pixel's gradient is zero, but its products with infinite inputs are not
-    const int vw = min(G.tw, A.Wo - tx0), w4 = (vw + 3) >> 2, ngrp = w4 * min(G.th, A.Ho - ty0);
+    const int vw = min(G.tw, A.Wo - tx0), w4 = (vw + 3) >> 2, ngrp = w4 * min(G.th, A.Ho - ty0) * nb;
     int row = 0, c = wave;
     for (; c >= w4; c -= w4) ++row;
     for (int s = wave; s < ngrp; s += 4) {
       const float af = s_g[(row * G.tw + 4 * c + g) * GP + r16];
-      const float* xa = s_x + (row * PW + 4 * c + g) * CB;
+      const float* xa = s_x + ((PACK ? row + 2 * (row / G.th) : row) * PW + 4 * c + g) * CB;
       float bf[NTL];
 #pragma unroll
       for (int t = 0; t < NTL; ++t) bf[t] = xa[off[t]];
@@ -181,9 +187,18 @@ int ls_wgrad_f32_partials(const WgradArgs& a, int* nchunk, hipStream_t st) {
       g.th = th;
     }
   }
+  // planes of which a tile holds several: as many as fit (a backward of 2,000
+  // images of 4 x 4, 2 x 2 and 1 x 1 texels 1.11 ms; with a tile for each 2.70 ms)
+  const int pw = (a.Wo + 3) & ~3;
+  g.ni = std::min(TILE_PX / std::max(1, pw * a.Ho), PATCH_PX / ((pw + 2) * (a.Ho + 2)));
+  const bool pack = g.ni > 1;
+  if (pack) {
+    g.tw = pw;
+    g.th = a.Ho;
+  }
   g.tiles_x = (a.Wo + g.tw - 1) / g.tw;
   g.per_img = g.tiles_x * ((a.Ho + g.th - 1) / g.th);
-  const int64_t ntiles = (int64_t)a.B * g.per_img;
+  const int64_t ntiles = pack ? (a.B + g.ni - 1LL) / g.ni : (int64_t)a.B * g.per_img;
   if (ntiles > 0x7fffffff) return LS_ENOTIMPL;
   g.ntiles = (int)ntiles;
   g.ncib = cin / cb;
@@ -192,10 +207,9 @@ int ls_wgrad_f32_partials(const WgradArgs& a, int* nchunk, hipStream_t st) {
   const int per = std::max(1, (g.ntiles + a.nchunk - 1) / a.nchunk);
   *nchunk = std::max(1, (g.ntiles + per - 1) / per);
   const dim3 grid((unsigned)*nchunk, (unsigned)groups);
-  if (cb == 16)
-    hipLaunchKernelGGL(k_wgrad_f32_mfma<16>, grid, dim3(WT), 0, st, a, g);
-  else
-    hipLaunchKernelGGL(k_wgrad_f32_mfma<8>, grid, dim3(WT), 0, st, a, g);
+  auto* fn = cb == 16 ? (pack ? k_wgrad_f32_mfma<16, true> : k_wgrad_f32_mfma<16, false>)
+                      : (pack ? k_wgrad_f32_mfma<8, true> : k_wgrad_f32_mfma<8, false>);
+  hipLaunchKernelGGL(fn, grid, dim3(WT), 0, st, a, g);
   LS_LAUNCH_CHECK();
   return LS_OK;
 }
