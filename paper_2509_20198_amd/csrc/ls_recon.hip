@@ -1014,6 +1014,7 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
   // between them the sort keys and entries of a window that fits
   __shared__ __align__(16) int s_mem[PREP_INTS];
   __shared__ int s_tmp[RB / 64 + 1];
+  __shared__ int s_repeats;  // points at positions that others share
   const int tid = threadIdx.x;
   const int R = P.R, H = P.H, W2 = 2 * P.H;
   const int RR = R * R;
@@ -1042,6 +1043,7 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
   int* s_b = s_mem;
   int* s_k = s_mem + PREP_INTS - (NB + 1);
   // ---- a. gather + bucket histogram
+  if (tid == 0) s_repeats = 0;
   for (int b = tid; b <= NB; b += RB) s_b[b] = 0;
   __syncthreads();
   for (int e0 = tid; e0 < cnt; e0 += PREP_BATCH * RB) {
@@ -1121,44 +1123,22 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
     const int mm = __builtin_amdgcn_readfirstlane(block_scan_excl(s_k, NB + 1, s_tmp));
     for (int b = tid; b < NB; b += RB) {
       const int lo = s_b[b], hi = s_b[b + 1];
-      int w = s_k[b] - 1;
-      for (int i = lo; i < hi; ++i) {
-        if (i == lo || key[i] != key[i - 1]) {
-          const uint64_t kk = key[i];
-          ++w;
-          P.cuv[off + w] = make_int2((int)(uint32_t)kk - (1 << 20), (int)(uint32_t)(kk >> 32) - (1 << 20));
-          P.sslot[off + w] = idx[i];  // the slots have been used
-        }
-        if (mm < cnt) P.su[off + idx[i]] = w;  // and so have the coordinates
+      int w = s_k[b];
+      for (int i = lo; i < hi; ++w) {
+        const uint64_t kk = key[i];
+        P.cuv[off + w] = make_int2((int)(uint32_t)kk - (1 << 20), (int)(uint32_t)(kk >> 32) - (1 << 20));
+        P.sslot[off + w] = idx[i];  // the slots have been used
+        int j = i + 1;
+        while (j < hi && key[j] == kk) ++j;
+        if (j - i > 1)  // and so have the coordinates: entries of repeated positions and their points
+          for (int at = off + atomicAdd(&s_repeats, j - i); i < j; ++i, ++at) {
+            P.su[at] = idx[i];
+            P.sv[at] = w;
+          }
+        i = j;
       }
     }
     __syncthreads();
-    if (mm < cnt) {
-      // Repeated positions: the maximum of (z, R, G) over a position's points,
-      // then of B among those that reach it, in the space of the keys.  1000
-      // points at one position 0.43 ms; sorted with the positions, by one lane a
-      // bucket with two dependent reads a comparison, 63 ms.
-      unsigned long long* top = reinterpret_cast<unsigned long long*>(key);
-      for (int w = tid; w < mm; w += RB) {
-        __hip_atomic_store(top + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(idx + w, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      __syncthreads();
-      for (int e = tid; e < cnt; e += RB) atomicMax(top + P.su[off + e], top_of(P.bin_idx[off + e]));
-      __syncthreads();
-      for (int e = tid; e < cnt; e += RB) {
-        const int32_t gi = P.bin_idx[off + e], w = P.su[off + e];
-        if (__hip_atomic_load(top + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == top_of(gi))
-          atomicMax(idx + w, (int)P.rgb[3 * (int64_t)gi + 2]);
-      }
-      __syncthreads();
-      for (int w = tid; w < mm; w += RB) {
-        const unsigned long long v = __hip_atomic_load(top + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        P.cattr[off + w] = make_int4((int)((uint32_t)(v >> 32) ^ 0x80000000u), (int)((v >> 16) & 0xFFFF), (int)(v & 0xFFFF),
-                                     __hip_atomic_load(idx + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-      }
-      return mm;
-    }
     for (int w0 = tid; w0 < mm; w0 += PREP_BATCH * RB) {
       int32_t gi[PREP_BATCH];
       int4 at[PREP_BATCH];
@@ -1174,6 +1154,33 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
 #pragma unroll
       for (int j = 0; j < PREP_BATCH; ++j)
         if (w0 + j * RB < mm) P.cattr[off + w0 + j * RB] = at[j];
+    }
+    // Repeated positions: the maximum of (z, R, G) over a position's entries, then
+    // of B among those that reach it, in the space of the keys.  1000 points at
+    // one position 0.42 ms; sorted with the positions, by one lane a bucket with two
+    // dependent reads a comparison, 63 ms.
+    const int repeats = __builtin_amdgcn_readfirstlane(s_repeats);
+    if (repeats) {
+      unsigned long long* top = reinterpret_cast<unsigned long long*>(key);
+      for (int r = tid; r < repeats; r += RB) {
+        __hip_atomic_store(top + P.sv[off + r], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(idx + P.sv[off + r], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      __syncthreads();
+      for (int r = tid; r < repeats; r += RB) atomicMax(top + P.sv[off + r], top_of(P.bin_idx[off + P.su[off + r]]));
+      __syncthreads();
+      for (int r = tid; r < repeats; r += RB) {
+        const int32_t gi = P.bin_idx[off + P.su[off + r]], w = P.sv[off + r];
+        if (__hip_atomic_load(top + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == top_of(gi))
+          atomicMax(idx + w, (int)P.rgb[3 * (int64_t)gi + 2]);
+      }
+      __syncthreads();
+      for (int r = tid; r < repeats; r += RB) {
+        const int w = P.sv[off + r];
+        const unsigned long long v = __hip_atomic_load(top + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        P.cattr[off + w] = make_int4((int)((uint32_t)(v >> 32) ^ 0x80000000u), (int)((v >> 16) & 0xFFFF), (int)(v & 0xFFFF),
+                                     __hip_atomic_load(idx + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      }
     }
     return mm;
   };
