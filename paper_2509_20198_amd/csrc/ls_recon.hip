@@ -212,28 +212,44 @@ __global__ void __launch_bounds__(BIN_THREADS) k_bin_scatter_lds(BinParams p, in
 }
 
 constexpr int ORDER_KEYS = 4096;
+// Points of a window that may hold a triangle.  Smaller windows need no face map:
+// they come last in the processing order, behind the launches that hold some.
+constexpr int FACE_POINTS = 3;
 
 // Descending window count, in steps of 4 points, as an ascending key.
 __device__ __forceinline__ int order_key(int32_t count) {
-  return ORDER_KEYS - 1 - min(max(count, 0) >> 2, ORDER_KEYS - 1);
+  return count < FACE_POINTS ? ORDER_KEYS - 1 : ORDER_KEYS - 2 - min(count >> 2, ORDER_KEYS - 2);
 }
 
 // Single-workgroup exclusive scan of counts -> bin_off (n_tiles + 1 entries),
-// then the recon processing order: the caller's list order, or a counting
-// sort of the tile slots by order_key (slots with equal keys in any order;
-// the results do not depend on the order).
+// and the recon processing order: the caller's list order (windows without a
+// triangle behind the others, in reverse), or a counting sort of the tile slots
+// by order_key (slots with equal keys in any order; the results do not depend on
+// the order).
 __global__ void __launch_bounds__(1024) k_bin_scan(BinParams p) {
   __shared__ int64_t s_part[1024];
   __shared__ int64_t s_carry;
   __shared__ int s_hist[ORDER_KEYS];
+  __shared__ int s_faces[1024 / 64];
   const int tid = threadIdx.x;
+  int faces = 0;  // windows before these that may hold a triangle
   if (tid == 0) s_carry = 0;
   __syncthreads();
   for (int64_t base = 0; base < p.n_tiles; base += 1024) {
     const int64_t i = base + tid;
     const int64_t v = i < p.n_tiles ? p.counts[i] : 0;
     s_part[tid] = v;
+    const uint64_t with_face = __ballot(v >= FACE_POINTS);
+    if ((tid & 63) == 0) s_faces[tid >> 6] = __popcll(with_face);
     __syncthreads();
+    if (p.order_mode == LS_ORDER_LIST) {
+      int before = faces + __popcll(with_face & ((1ull << (tid & 63)) - 1));
+      for (int w = 0; w < 1024 / 64; ++w) {
+        before += w < (tid >> 6) ? s_faces[w] : 0;
+        faces += s_faces[w];
+      }
+      if (i < p.n_tiles) p.order[v >= FACE_POINTS ? before : p.n_tiles - 1 - ((int)i - before)] = (int)i;
+    }
     for (int o = 1; o < 1024; o <<= 1) {
       const int64_t t = tid >= o ? s_part[tid - o] : 0;
       __syncthreads();
@@ -251,10 +267,7 @@ __global__ void __launch_bounds__(1024) k_bin_scan(BinParams p) {
     p.bin_off[p.n_tiles] = (int32_t)(total < 0x7fffffff ? total : 0x7fffffff);
     p.flags[0] = total > p.cap ? 1 : 0;
   }
-  if (p.order_mode == LS_ORDER_LIST) {
-    for (int i = tid; i < p.n_tiles; i += 1024) p.order[i] = i;
-    return;
-  }
+  if (p.order_mode == LS_ORDER_LIST) return;
   constexpr int PER = ORDER_KEYS / 1024;
   for (int b = tid; b < ORDER_KEYS; b += 1024) s_hist[b] = 0;
   __syncthreads();
@@ -354,7 +367,7 @@ struct ReconParams {
   // per tile slot
   int32_t* npts;   // canonical points
   int32_t* has_dt; // 1: at least three points, not all collinear
-  uint64_t* facemap;  // R * R texels of every tile of the launch
+  uint64_t* facemap;  // R * R texels of every tile of the launch; null where none has a triangle
   int2* items;        // work items of the stars: position of the tile in the launch, first point
   int32_t* item_n;    // how many, then by XCD how many of its range are taken, ITEM_COUNTER apart
   int32_t item;       // points of an item
@@ -1035,8 +1048,10 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
     return;
   }
   // texels without a triangle until the stars fill them in
-  uint64_t* __restrict__ fm = P.facemap + (int64_t)blockIdx.x * RR;
-  for (int tt = tid; tt < RR; tt += RB) fm[tt] = FACE_NONE;
+  if (P.facemap) {
+    uint64_t* __restrict__ fm = P.facemap + (int64_t)blockIdx.x * RR;
+    for (int tt = tid; tt < RR; tt += RB) fm[tt] = FACE_NONE;
+  }
   const int64_t cx = P.ox + (int64_t)(t % P.tiles_x) * P.S + P.S / 2;
   const int64_t cy = P.oy + (int64_t)(t / P.tiles_x) * P.S + P.S / 2;
   const int G = bucket_side(cnt), NB = G * G;
@@ -1550,6 +1565,7 @@ __global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
   const int cnt = __builtin_amdgcn_readfirstlane(P.bin_off[k + 1]) - off;
   const int R = P.R, C = P.C;
   const int G = bucket_side(cnt), NB = G * G;
+  const bool faces = P.facemap != nullptr;
   const uint64_t* __restrict__ fm = P.facemap + (int64_t)pos * R * R;
   // coordinates, three far points, bucket offsets
   const bool lds = 2 * (m + 3) + NB + 1 <= OUT_INTS;
@@ -1601,7 +1617,7 @@ __global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
     // c_z: the centre texel; outside the hull (sparse windows) its nearest
     // point is searched by all lanes
     const int ic = R / 2;
-    const uint64_t fc = fm[ic * R + ic];
+    const uint64_t fc = faces ? fm[ic * R + ic] : FACE_NONE;
     int pc = -1;
     if (__builtin_amdgcn_readfirstlane((int)(fc == FACE_NONE))) {
       const int qc = q0 + ic * C;
@@ -1646,7 +1662,7 @@ __global__ void __launch_bounds__(TB) k_recon_out(ReconParams P, int parts) {
       const int bi = blk / nbs, i0 = 8 * bi + di, j0 = 8 * (blk - bi * nbs) + dj;
       const int i = i0 + ((lane >> 2) & 3), j = j0 + (lane & 3);
       const bool in_grid = i < R && j < R;
-      const uint64_t f = in_grid ? fm[i * R + j] : FACE_NONE;
+      const uint64_t f = in_grid && faces ? fm[i * R + j] : FACE_NONE;
       const int p = nearest_of_texel(T, q0, C, R, min(i0, R - 1), min(j0, R - 1), i, j);
       if (!in_grid) continue;
       const int4 near = attr[p];
@@ -1877,7 +1893,6 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
   rp.boff = L.sort_scratch;  // free once the caller's CSR is sorted
   rp.npts = L.fill;          // free once the points are binned
   rp.has_dt = L.counts;
-  rp.facemap = L.facemap;
   rp.items = L.items;
   rp.item_n = L.flags + ITEM_COUNTER;
   rp.order = L.order;
@@ -1886,18 +1901,24 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
   rp.status = tile_status;
   {
     LS_TRACE("recon_tile", st);
-    // as many tiles at a time as the workspace holds face maps for
+    // As many tiles at a time as the workspace holds face maps for.  At most
+    // n_face windows hold FACE_POINTS points, and these come first; the others
+    // are one launch without face maps (16384 tiles with 1000 points in all:
+    // 1.16 ms, 1.84 in rounds over every tile).
+    const int n_face = (int)std::min<int64_t>(n_tiles, (L.entries - 1) / FACE_POINTS);
     for (int q0 = 0; q0 < n_tiles;) {
-      const int nt = (int)std::min<int64_t>(n_tiles - q0, std::min<int64_t>(L.face_tiles, 1 << 20));
+      const bool faces = q0 < n_face;
+      const int nt = (int)std::min<int64_t>(faces ? std::min<int64_t>(n_face - q0, L.face_tiles) : n_tiles - q0, 1 << 20);
       const int parts = recon_out_parts(nt);
       rp.q0 = q0;
+      rp.facemap = faces ? L.facemap : nullptr;
       // few tiles: a wave takes the points it works on at once
       rp.item = nt <= 64 ? ITEM_MIN : ITEM_MAX;
-      if (q0) hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(T), 0, st, rp.item_n,
-                         (int64_t)(N_FLAGS - ITEM_COUNTER), 0);
+      if (q0 && faces)
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(T), 0, st, rp.item_n, (int64_t)(N_FLAGS - ITEM_COUNTER), 0);
       hipLaunchKernelGGL(k_recon_prep, dim3(nt), dim3(RB), 0, st, rp);
-      hipLaunchKernelGGL(k_recon_stars, dim3(3 * ((num_cus() + XCDS - 1) / XCDS * XCDS)), dim3(TB), 0,
-                         st, rp);
+      if (faces)
+        hipLaunchKernelGGL(k_recon_stars, dim3(3 * ((num_cus() + XCDS - 1) / XCDS * XCDS)), dim3(TB), 0, st, rp);
       hipLaunchKernelGGL(k_recon_out, dim3((unsigned)nt * parts), dim3(TB), 0, st, rp, parts);
       q0 += nt;
     }
