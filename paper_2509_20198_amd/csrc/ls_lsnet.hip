@@ -310,7 +310,7 @@ typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 // Bound by the latency of its loads: the sums run over K in order, so a tile is
 // one serial chain of K / 32 steps.  Hence STEPS steps of loads are in flight
 // before the products of the last STEPS, and a wave has one column tile where
-// four would leave the chip short of waves: 333 x 512 x 4608 in 36 us (84 us with
+// four would leave the chip short of waves: 333 x 512 x 4608 in 35 us (84 us with
 // four column tiles and a step's loads at a time; 12 or 16 steps in flight give
 // no more).
 template <int NT, int STEPS>
@@ -541,9 +541,13 @@ int fc_f32(const float* A, const float* B, const float* bias, float* C, int M, i
 int fc_bf16(const uint16_t* A, const uint16_t* W, const float* bias, uint16_t* C, int M, int N, int K,
             hipStream_t st) {
   if (N % 64 || K % 32) return LS_ENOTIMPL;
-  // four column tiles a wave read A a quarter as often, once that still gives a
-  // wave to every other SIMD: 333 x 2304 x 512 in 14 us, 20 us with one
-  const bool wide = (int64_t)(N / 64) * ((M + 15) / 16) >= 512;
+  // Four column tiles a wave read A a quarter as often, but its chain of K steps
+  // takes twice as long: worth it once one column tile would give a SIMD more than
+  // two waves, which it takes in turn.  512 x 4608 (FC1) of 1024 rows, two waves:
+  // 67 us with one column tile, 82 with four; 1024 x 512, 512 rows, two waves: 13.0
+  // and 13.7, 768 rows, three waves: 18.5 and 14.1; 2304 x 512 (FC2), 333 rows: 19.6
+  // and 13.8.
+  const bool wide = (int64_t)(N / 64) * ((M + 15) / 16) > 512;
   LS_TRACE("fc_bf16", st);
   const unsigned rows = (unsigned)((M + 63) / 64);
   if (wide)
