@@ -1720,9 +1720,16 @@ int64_t max_multiplicity(const LsGridInfo& gi) {
   return per * per;
 }
 
-// Output workgroups of a tile: about 4,096 in a launch, so that a few tiles still
-// fill the chip and the largest windows do not end last.
-int recon_out_parts(int nt) { return std::min(36, std::max(2, 4096 / nt)); }
+// Output workgroups of a tile, each with a block of 8 x 8 texels for its four waves
+// at least: about 4,096 in a launch, so that the largest windows do not end last,
+// but no more than 36 of a tile (each copies its window's points first: 64 tiles of
+// 224 x 224 texels 257 us, with 64 of a tile 261) unless the launch has fewer than
+// 2,048 (one tile of 544 x 544 texels and 400 points: 248 us with 36, 190 with all
+// its 1,156; of 100,000 points 4.57 and 4.07 ms).
+int recon_out_parts(int nt, int R) {
+  const int64_t nbs = (R + 7) / 8, most = (nbs * nbs + TB / 64 - 1) / (TB / 64);
+  return (int)std::min<int64_t>(most, std::max({2, std::min(36, 4096 / nt), 2048 / nt}));
+}
 
 int recon_wg_count(int32_t n_tiles) {
   const int want = 2 * num_cus();
@@ -1909,7 +1916,7 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
     for (int q0 = 0; q0 < n_tiles;) {
       const bool faces = q0 < n_face;
       const int nt = (int)std::min<int64_t>(faces ? std::min<int64_t>(n_face - q0, L.face_tiles) : n_tiles - q0, 1 << 20);
-      const int parts = recon_out_parts(nt);
+      const int parts = recon_out_parts(nt, gi.R);
       rp.q0 = q0;
       rp.facemap = faces ? L.facemap : nullptr;
       // few tiles: a wave takes the points it works on at once
