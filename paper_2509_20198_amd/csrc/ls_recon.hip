@@ -86,6 +86,7 @@ struct BinParams {
   int32_t* flags;  // [0]: cap overflow
   int32_t* order;  // recon processing order (tile slots)
   int32_t order_mode;  // LS_ORDER_LIST or LS_ORDER_LONGEST_FIRST
+  int32_t n_face;  // most windows that may hold a triangle
 };
 
 // floor(a / S) for |a| < 2^53: the double quotient is within one of it
@@ -222,16 +223,17 @@ __device__ __forceinline__ int order_key(int32_t count) {
 }
 
 // Single-workgroup exclusive scan of counts -> bin_off (n_tiles + 1 entries),
-// and the recon processing order: the caller's list order (windows without a
-// triangle behind the others, in reverse), or a counting sort of the tile slots
-// by order_key (slots with equal keys in any order; the results do not depend on
-// the order).
+// and the recon processing order: the caller's list order (where not all windows
+// can hold a triangle, those that do not behind the others, in reverse), or a
+// counting sort of the tile slots by order_key (slots with equal keys in any order;
+// the results do not depend on the order).
 __global__ void __launch_bounds__(1024) k_bin_scan(BinParams p) {
   __shared__ int64_t s_part[1024];
   __shared__ int64_t s_carry;
   __shared__ int s_hist[ORDER_KEYS];
   __shared__ int s_faces[1024 / 64];
   const int tid = threadIdx.x;
+  const bool part = p.order_mode == LS_ORDER_LIST && p.n_face < p.n_tiles;
   int faces = 0;  // windows before these that may hold a triangle
   if (tid == 0) s_carry = 0;
   __syncthreads();
@@ -242,7 +244,7 @@ __global__ void __launch_bounds__(1024) k_bin_scan(BinParams p) {
     const uint64_t with_face = __ballot(v >= FACE_POINTS);
     if ((tid & 63) == 0) s_faces[tid >> 6] = __popcll(with_face);
     __syncthreads();
-    if (p.order_mode == LS_ORDER_LIST) {
+    if (part) {
       int before = faces + __popcll(with_face & ((1ull << (tid & 63)) - 1));
       for (int w = 0; w < 1024 / 64; ++w) {
         before += w < (tid >> 6) ? s_faces[w] : 0;
@@ -267,7 +269,10 @@ __global__ void __launch_bounds__(1024) k_bin_scan(BinParams p) {
     p.bin_off[p.n_tiles] = (int32_t)(total < 0x7fffffff ? total : 0x7fffffff);
     p.flags[0] = total > p.cap ? 1 : 0;
   }
-  if (p.order_mode == LS_ORDER_LIST) return;
+  if (p.order_mode == LS_ORDER_LIST) {
+    for (int i = tid; i < p.n_tiles && !part; i += 1024) p.order[i] = i;
+    return;
+  }
   constexpr int PER = ORDER_KEYS / 1024;
   for (int b = tid; b < ORDER_KEYS; b += 1024) s_hist[b] = 0;
   __syncthreads();
@@ -1839,6 +1844,8 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
   bp.flags = L.flags;
   bp.order = L.order;
   bp.order_mode = order;
+  const int n_face = (int)std::min<int64_t>(n_tiles, (L.entries - 1) / FACE_POINTS);
+  bp.n_face = n_face;
   const int pb = (int)std::min<int64_t>((n + T - 1) / T, 8192);
   // workgroup-private histograms when the tile list fits in LDS
   const bool lds_bins = n_tiles <= BIN_LDS_TILES;
@@ -1912,7 +1919,6 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
     // n_face windows hold FACE_POINTS points, and these come first; the others
     // are one launch without face maps (16384 tiles with 1000 points in all:
     // 1.16 ms, 1.84 in rounds over every tile).
-    const int n_face = (int)std::min<int64_t>(n_tiles, (L.entries - 1) / FACE_POINTS);
     for (int q0 = 0; q0 < n_tiles;) {
       const bool faces = q0 < n_face;
       const int nt = (int)std::min<int64_t>(faces ? std::min<int64_t>(n_face - q0, L.face_tiles) : n_tiles - q0, 1 << 20);
