@@ -1143,21 +1143,29 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
     const int mm = __builtin_amdgcn_readfirstlane(block_scan_excl(s_k, NB + 1, s_tmp));
     for (int b = tid; b < NB; b += RB) {
       const int lo = s_b[b], hi = s_b[b + 1];
-      int w = s_k[b];
-      for (int i = lo; i < hi; ++w) {
-        const uint64_t kk = key[i];
-        P.cuv[off + w] = make_int2((int)(uint32_t)kk - (1 << 20), (int)(uint32_t)(kk >> 32) - (1 << 20));
-        P.sslot[off + w] = idx[i];  // the slots have been used
-        int j = i + 1;
-        while (j < hi && key[j] == kk) ++j;
-        if (j - i > 1)  // and so have the coordinates: entries of repeated positions and their points
-          for (int at = off + atomicAdd(&s_repeats, j - i); i < j; ++i, ++at) {
-            P.su[at] = idx[i];
-            P.sv[at] = w;
-          }
-        i = j;
-      }
+      int w = off + s_k[b];
+      for (int i = lo; i < hi; ++i)
+        if (i == lo || key[i] != key[i - 1]) {
+          const uint64_t kk = key[i];
+          P.cuv[w] = make_int2((int)(uint32_t)kk - (1 << 20), (int)(uint32_t)(kk >> 32) - (1 << 20));
+          P.sslot[w] = idx[i];  // the slots have been used
+          ++w;
+        }
     }
+    if (mm < cnt)  // and so have the coordinates: entries at repeated positions and their points
+      for (int b = tid; b < NB; b += RB) {
+        const int hi = s_b[b + 1];
+        for (int i = s_b[b], w = s_k[b]; i < hi; ++w) {
+          int j = i + 1;
+          while (j < hi && key[j] == key[i]) ++j;
+          if (j - i > 1)
+            for (int at = off + atomicAdd(&s_repeats, j - i); i < j; ++i, ++at) {
+              P.su[at] = idx[i];
+              P.sv[at] = w;
+            }
+          i = j;
+        }
+      }
     __syncthreads();
     for (int w0 = tid; w0 < mm; w0 += PREP_BATCH * RB) {
       int32_t gi[PREP_BATCH];
@@ -1179,8 +1187,8 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
     // of B among those that reach it, in the space of the keys.  1000 points at
     // one position 0.42 ms; sorted with the positions, by one lane a bucket with two
     // dependent reads a comparison, 63 ms.
-    const int repeats = __builtin_amdgcn_readfirstlane(s_repeats);
-    if (repeats) {
+    if (mm < cnt) {
+      const int repeats = s_repeats;
       unsigned long long* top = reinterpret_cast<unsigned long long*>(key);
       for (int r = tid; r < repeats; r += RB) {
         __hip_atomic_store(top + P.sv[off + r], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
