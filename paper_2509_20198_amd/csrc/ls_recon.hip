@@ -371,7 +371,6 @@ struct ReconParams {
   int32_t* boff;   // 2 per bin entry: canonical bucket offsets of a tile from 2 * its bin offset on
   // per tile slot
   int32_t* npts;   // canonical points
-  int32_t* has_dt; // 1: at least three points, not all collinear
   uint64_t* facemap;  // R * R texels of every tile of the launch; null where none has a triangle
   int2* items;        // work items of the stars: position of the tile in the launch, first point
   int32_t* item_n;    // how many, then by XCD how many of its range are taken, ITEM_COUNTER apart
@@ -1048,7 +1047,6 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
       P.cz_out[k] = 0.0;
       P.status[k] = flags | LS_TILE_EMPTY;
       P.npts[k] = 0;
-      P.has_dt[k] = 0;
     }
     return;
   }
@@ -1234,7 +1232,6 @@ __global__ void __launch_bounds__(RB) k_recon_prep(ReconParams P) {
   const bool dt = __syncthreads_or(noncol) != 0 && !big;
   if (tid == 0) {
     P.npts[k] = m;
-    P.has_dt[k] = dt ? 1 : 0;
     P.status[k] = flags | (dt ? 0 : LS_TILE_NN_ONLY) | (big ? LS_TILE_DEGENERATE : 0);
   }
   if (dt) {
@@ -1914,7 +1911,6 @@ int recon_enqueue(const LsGridInfo& gi, const int32_t* x, const int32_t* y, cons
   rp.cattr = L.cattr;
   rp.boff = L.sort_scratch;  // free once the caller's CSR is sorted
   rp.npts = L.fill;          // free once the points are binned
-  rp.has_dt = L.counts;
   rp.items = L.items;
   rp.item_n = L.flags + ITEM_COUNTER;
   rp.order = L.order;
