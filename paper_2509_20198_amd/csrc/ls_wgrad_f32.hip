@@ -9,12 +9,14 @@
 // lane groups, so no transpose is needed), every element once for its nine
 // taps.  Its four waves take every fourth group of four pixels, and their sums
 // are added in LDS in a fixed order, so the partial sums are deterministic.
-// Tiles are about 256 pixels, 8 to 32 wide, whichever pads the plane least
-// (24 x 8 on the 24-wide planes); several whole images one above the other where
-// a plane has at most 10 x 10 texels.
+// Tiles are about 256 pixels, 16 to 32 wide, whichever pads the plane least
+// (24 x 8 on the 24-wide planes; windows are square, so 8 x 32 would pad as much
+// as 32 x 8); several whole images one above the other where a plane has at most
+// 10 x 10 texels.
 //
 // Bound: at small batches the exposed staging of the one or two tiles a
-// workgroup gets, else the matrix cores (ten products per ten LDS reads).  24
+// workgroup gets, else the matrix cores (nine products per ten LDS reads, ten
+// where the bias is summed; five per six with 8 input channels).  24
 // tiles of 96 x 96, all eleven layers: 0.32 ms (40 TFLOP/s); 0.75 ms with the
 // vector kernel this replaced, which staged the im2col columns (each input
 // element nine times).  32 output channels per workgroup took 232 registers
@@ -30,7 +32,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int WT = 256;         // threads
 constexpr int TILE_PX = 256;    // output pixels of a tile at most
-constexpr int PATCH_PX = 340;   // and its input patch: 10 x 34, 18 x 18, 26 x 10, 34 x 10
+constexpr int PATCH_PX = 340;   // and its input patch: 18 x 18, 26 x 10, 34 x 10
 
 struct WgradGeom {
   int tw, th;              // tile, tw a multiple of 4
@@ -178,7 +180,7 @@ int ls_wgrad_f32_partials(const WgradArgs& a, int* nchunk, hipStream_t st) {
   const int cb = a.src.a.c % 16 == 0 && a.src.b.c % 16 == 0 ? 16 : 8;
   WgradGeom g;
   int64_t best = 0;
-  for (int tw : {16, 24, 32, 8}) {
+  for (int tw : {16, 24, 32}) {
     const int th = tw == 24 ? 8 : TILE_PX / tw;
     const int64_t padded = (int64_t)((a.Wo + tw - 1) / tw) * tw * (((a.Ho + th - 1) / th) * th);
     if (best == 0 || padded < best) {
