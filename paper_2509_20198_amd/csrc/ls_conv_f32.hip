@@ -318,8 +318,9 @@ ConvPlan conv_plan(const ConvArgs& a) {
 template <int KB, int NT, bool MASK>
 int launch(const ConvArgs& a, const ConvPlan& p, hipStream_t st) {
   auto* fn = k_conv_f32_mfma<KB, NT, MASK>;
+  // the same limit whatever this launch needs: another thread may set it for its own
   if (p.lds > 65536)
-    LS_HOST_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, p.lds));
+    LS_HOST_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MAX));
   hipLaunchKernelGGL(fn, dim3((unsigned)p.g.chunk * 8), dim3(64u * p.g.wx * p.g.wy * p.g.wm), p.lds, st, a, p.g);
   LS_LAUNCH_CHECK();
   return LS_OK;
