@@ -74,13 +74,17 @@ typedef enum ls_tile_flag {
 
 typedef enum ls_precision { LS_FP32 = 0, LS_BF16 = 1 } ls_precision;
 
-/* Order in which ls_recon_tiles takes its tiles from the work queue.
- *  LS_ORDER_LIST: the order of tile_list, e.g. by distance to the viewer, so
- *    that construction is prioritised towards the viewpoint (Section 1 and
- *    the Section 4.1 discussion of Table 2: nearby heightmaps first).
- *  LS_ORDER_LONGEST_FIRST: descending window point count (in steps of 4
- *    points), so the last tiles to start are short and the workgroups finish
- *    together; for throughput on a batch with no priority.
+/* Order in which ls_recon_tiles starts its tiles.  A call takes as many tiles
+ * at a time as its workspace holds face maps for (all 1,024 of a batch, about
+ * 5,000 of the 16,384-tile set), and the tiles of one such round are finished
+ * together, whatever their order: a caller that wants the nearest heightmaps
+ * first (Section 1 and the Section 4.1 discussion of Table 2) passes them in a
+ * call of their own.
+ *  LS_ORDER_LIST: rounds and starts in the order of tile_list; where most of a
+ *    long list cannot hold three points, the windows that do come first.
+ *  LS_ORDER_LONGEST_FIRST: by descending window point count (in steps of 4
+ *    points), so the last tiles to start in a round are short; for throughput
+ *    on a batch with no priority.
  * Results per output slot do not depend on the order. */
 typedef enum ls_order { LS_ORDER_LIST = 0, LS_ORDER_LONGEST_FIRST = 1 } ls_order;
 
@@ -113,9 +117,8 @@ size_t ls_act_bytes(const ls_grid* g, int32_t n_tiles, int precision);
  *  x, y, z [n] int32 raw; rgb [n][3] uint16 (16-bit LAS colour).
  *  tile_list [n_tiles]: linear tile ids ty*tiles_x + tx, distinct.  Output
  *    slot k belongs to tile_list[k].
- *  order: ls_order; LS_ORDER_LIST processes the tiles in tile_list order
- *    (workgroups take them from a queue in that order), LS_ORDER_LONGEST_FIRST
- *    by descending window point count.  Other values: LS_ERANGE.
+ *  order: ls_order, the order in which tiles are started.  Other values:
+ *    LS_ERANGE.
  *  x_out [n_tiles][R][R][8] FP32: channel 0 (h_lin - cz)/r, 1 (h_nn - cz)/r,
  *    2-4 linear RGB/65535, 5-7 nearest RGB/65535, with r = H*scale_xy
  *    metres and h in metres.
@@ -141,11 +144,11 @@ int ls_recon_tiles(const ls_grid* g, const int32_t* x, const int32_t* y, const i
  * LS_RECON_SCRATCH_BYTES in device memory instead, which every device the
  * call runs on holds until the process ends.  The call allocates nothing.
  * Limit: LS_ESCRATCH (nothing enqueued) when the inputs need more than the
- * array with a single persistent workgroup (per point of n about 600 bytes,
- * per tile of the region 4 bytes, per listed tile 20 bytes, plus 12*R*R
- * bytes per workgroup: about 80,000 points with the 96 x 96 grid); inputs
- * that fit run on as many workgroups as the array holds (fewer than
- * ls_recon_tiles uses when the points fill most of it, so slower).
+ * array (per point of n about 600 bytes, per tile of the region 4 bytes, per
+ * listed tile 20 bytes, plus 12*R*R bytes: about 80,000 points with the
+ * 96 x 96 grid).  The points' arrays take less than that; what they leave
+ * holds face maps of 8*R*R bytes, and a call with more tiles than face maps
+ * runs in several rounds.
  * Every call on one GPU shares its array and leaves its contents behind;
  * calls that overlap on one GPU (other streams, other threads) race on it,
  * so serialise them. */

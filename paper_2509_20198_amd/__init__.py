@@ -215,8 +215,8 @@ def recon_tiles(grid, x, y, z, rgb, tile_list, *, order: int = ORDER_LIST, x_out
                 bin_idx=None, bin_cap: int = 0, status=None, ws=None, stream=None):
     """Binning + Algorithm 1 + normalisation -> (x_out [n,R,R,8] f32, cz [n] f64, status [n] i32).
 
-    order: ORDER_LIST processes the tiles in tile_list order (viewpoint
-    priority), ORDER_LONGEST_FIRST by descending window point count."""
+    order: ORDER_LIST starts the tiles in tile_list order (the tiles of one round of launches
+    are finished together), ORDER_LONGEST_FIRST by descending window point count."""
     lib = load_library()
     g = Grid.of(grid)
     n = x.numel()

@@ -2,8 +2,8 @@
 
 Every (layer, precision, pass) has a small set of tilings (see
 ls_conv_num_configs: direct / LDS-staged tile / pixel tiles per wave for
-BF16, channel-block width for FP32, pixel-chunk count for the weight
-gradient).  All tilings of a (layer, precision, pass) compute the same
+BF16, pixels and waves per workgroup for FP32, number of partial sums for the
+weight gradient).  All tilings of a (layer, precision, pass) compute the same
 result; they differ only in speed for a given shape.  The tuner times the
 whole forward (pass 0) or forward + backward (passes 1, 2) on the real batch
 shape with HIP events, changing one layer at a time (coordinate descent,

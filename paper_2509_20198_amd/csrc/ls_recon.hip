@@ -8,8 +8,8 @@
 //      4 windows with the paper's 16-texel ring).
 //   3. k_bin_sort (only when the caller asks for the CSR): ascending order.
 //   4. for as many tiles at a time as the workspace holds face maps, in the
-//      caller's list order (viewpoint priority) or by descending window point
-//      count:
+//      caller's list order or by descending window point count, the tiles that
+//      cannot hold a triangle at the end:
 //      k_recon_prep, one workgroup per tile:
 //        a. gather the tile's points to tile-local coordinates and bucket
 //           them into a G x G grid over the window (LDS counting sort);
@@ -46,7 +46,7 @@
 namespace {
 
 constexpr int RB = 512;                  // threads of a preparation workgroup
-constexpr int PREP_INTS = 12000;         // its LDS: windows up to about 3,000 points sort there
+constexpr int PREP_INTS = 12000;         // its LDS: windows up to 2,644 points sort there
 constexpr int PREP_BATCH = 4;            // points a lane reads at a time
 constexpr int MAXG = 76;                 // max buckets per side
 constexpr int MAXB = MAXG * MAXG;        // max buckets
@@ -1746,7 +1746,7 @@ int recon_wg_count(int32_t n_tiles) {
   return n_tiles < want ? (n_tiles > 0 ? n_tiles : 1) : want;
 }
 
-// Workspace bytes for n_tiles tiles and n points: 144 bytes per bin entry
+// Workspace bytes for n_tiles tiles and n points: 148 bytes per bin entry
 // plus 12 R^2 per tile of a launch (at most two per CU count), and the lists.
 // These are the sizes and limits callers know; the arrays take less, and the
 // rest of the space holds face maps.

@@ -1675,7 +1675,11 @@ int ls_bf16_forward(const float* w, const uint16_t* packed, const float* x, int 
   // layer pairs (enc1a, enc1b) and (dec1b, head) in one pass when their
   // first activation is not kept: config 4 of the pair's second layer, the
   // default for the head (measured on 1024 tiles: dec1b + head 0.230 ->
-  // 0.170 ms; enc1a + enc1b 0.261 -> 0.267 ms, so separate by default)
+  // 0.170 ms).  enc1a + enc1b are separate unless config 4 is set: the pair was
+  // no faster while it stored all of A2; since it stores the window that dec1a
+  // reads, the whole forward takes 1308 us with the pair separate and 1283 with
+  // it fused (1024 tiles, ring of 16 texels; 406 and 400 at 256, 120 and 115 at
+  // 16; without a ring 750 and 748, 258 and 260, 109 and 107)
   auto fused = [&](int l2) {
     const int c = ls_conv_config_get(l2, LS_BF16, 0);
     return fuse && (c == 4 || (c < 0 && l2 == LS_NLAYER - 1));

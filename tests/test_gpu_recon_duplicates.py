@@ -24,7 +24,7 @@ def _repeated(n, positions, levels, seed):
     return (u[k] + 32000).astype(np.int32), (v[k] + 32000).astype(np.int32), z, rgb
 
 
-# windows up to about 2,600 points sort in LDS, larger ones in global memory
+# windows up to 2,644 points sort in LDS, larger ones in global memory
 @pytest.mark.parametrize("n,positions", [(600, 10), (2, 1), (900, 1), (500, 499), (2640, 40), (2700, 40), (6000, 4000)])
 @pytest.mark.parametrize("levels", [2, 7])
 def test_repeated_positions(n, positions, levels):
