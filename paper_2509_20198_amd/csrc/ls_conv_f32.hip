@@ -70,12 +70,16 @@ struct ConvGeom {
 };
 
 // The sums of a wave that are NaN, of pixels next to the border, in the order of
-// the products: without the taps outside the plane or outside a part's tensor.
+// the products: without the taps outside the plane or outside a part's tensor.  A
+// sum that is NaN again after a block of channels ends there (99 tiles with one
+// weight in a hundred infinite 1.42 ms, channel by channel to the end 5.6; 1.74 with
+// a vector kernel that skipped the taps).
 // px: the lane's staged pixel at tap (0, 0) of its first pixel tile.
 template <int KB, int NT>
 __device__ __forceinline__ void sums_within(const ConvArgs& A, const ConvGeom& G, f32x4 (&acc)[NT], const float* px,
                                             int PW, int SP, int mw, int g, int oy, int ox) {
   constexpr int V = KB / 4;
+  typedef typename VecOf<V>::T vec;
   const int ca = A.src.a.c, cin = ca + A.src.b.c, co = mw * 16 + 4 * g, x = A.x0 + ox;
   auto holds = [&](const SrcPart& p, int yy, int xx) {
     const int sy = p.up ? yy >> 1 : yy - p.oy, sx = p.up ? xx >> 1 : xx - p.ox;
@@ -92,14 +96,22 @@ __device__ __forceinline__ void sums_within(const ConvArgs& A, const ConvGeom& G
       continue;
     float s = A.bias ? A.bias[co + (e & 3)] : 0.f;
 #pragma unroll 1
-    for (int tap = 0; tap < 9; ++tap) {
+    for (int tap = 0; tap < 9 && s == s; ++tap) {
       const int ky = tap / 3, kx = tap - 3 * ky;
       const bool in_a = holds(A.src.a, y + ky - 1, x + kx - 1), in_b = holds(A.src.b, y + ky - 1, x + kx - 1);
-      const float* wt = A.wt + (int64_t)(mw * 9 + tap) * cin * 16 + (4 * g + (e & 3)) * V;
+      const float* in = px + (ky * PW + kx) * SP;
+      const vec* wt = reinterpret_cast<const vec*>(A.wt) + (mw * 9 + tap) * (cin / KB) * 64 + 4 * g + (e & 3);
 #pragma unroll 1
-      for (int ci = 0; ci < cin; ++ci)
-        if (ci < ca ? in_a : in_b)
-          s = fmaf(px[(ky * PW + kx) * SP + ci], wt[((ci / KB) * 64 + (ci & 3) * 16) * V + ((ci % KB) >> 2)], s);
+      for (int c0 = 0; c0 < cin && s == s; c0 += KB, wt += 64) {
+        const vec w[4] = {wt[0], wt[16], wt[32], wt[48]};  // channels c0 + k + 4 q
+#pragma unroll
+        for (int q = 0; q < V; ++q)
+          if (c0 + 4 * q < ca ? in_a : in_b) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(in + c0 + 4 * q);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) s = fmaf(v[k], w[k][q], s);
+          }
+      }
     }
 #pragma unroll
     for (int k = 0; k < 4 * NT; ++k) acc[k >> 2][k & 3] = k == e ? s : acc[k >> 2][k & 3];

@@ -77,3 +77,54 @@ def test_inputs_outside_the_heads_window(res, pad):
     torch.cuda.synchronize()
     assert torch.isfinite(want).all()
     assert torch.equal(got[-HEAD:], want[-HEAD:])
+
+
+def _planes(g, n, act):
+    """The saved FP32 activations A1 .. A10 and the two pooled ones."""
+    f = act.cpu().numpy().view(np.float32).astype(np.float64)
+    shapes = {"A1": (16, 1), "A2": (16, 1), "P1": (16, 2), "A3": (32, 2), "A4": (32, 2), "P2": (32, 4), "A5": (64, 4),
+              "A6": (64, 4), "A7": (32, 2), "A8": (32, 2), "A9": (16, 1), "A10": (16, 1)}
+    out, at = {}, 0
+    for k, (c, s) in shapes.items():
+        m = n * (g.R // s) ** 2 * c
+        out[k] = f[at:at + m].reshape(n, g.R // s, g.R // s, c)
+        at += m
+    return out
+
+
+def _conv(x, w, b):
+    """3x3 conv without the taps outside the plane, then max(., 0) with NaN to 0, as the kernels' fmaxf."""
+    n, h, wd, cin = x.shape
+    w = w.reshape(-1, 3, 3, cin)
+    s = np.broadcast_to(b, (n, h, wd, len(b))).copy()
+    for ky in range(3):
+        for kx in range(3):
+            oy, ox = slice(max(0, 1 - ky), min(h, h + 1 - ky)), slice(max(0, 1 - kx), min(wd, wd + 1 - kx))
+            iy, ix = slice(max(0, ky - 1), min(h, h + ky - 1)), slice(max(0, kx - 1), min(wd, wd + kx - 1))
+            with np.errstate(invalid="ignore"):
+                s[:, oy, ox] += (x[:, iy, ix, None, :] * w[None, None, None, :, ky, kx, :]).sum(-1)
+    return np.where(s > 0, s, 0.0)
+
+
+@pytest.mark.parametrize("layer", range(10))
+@pytest.mark.parametrize("value", [np.inf, -np.inf])
+def test_every_layer_on_its_own_inputs(layer, value):
+    """Infinite weights at three taps of one hidden layer; its saved output
+    against a 64-bit conv of its saved inputs."""
+    g, w, x, gy = _case(20, 0, 9)
+    shapes = [(ci, co) for _, ci, co in synth.UNET_SHAPES]
+    off = sum(co * 9 * ci + co for ci, co in shapes[:layer])
+    ci, co = shapes[layer]
+    wl = w[off:off + co * 9 * ci].reshape(co, 9, ci)
+    wl[1, 0, 0] = wl[co - 1, 5, ci - 1] = wl[co // 2, 7, ci // 2] = value
+    act = torch.empty(ls.act_bytes(g, 2, ls.FP32), dtype=torch.uint8, device="cuda")
+    ls.refine_tiles(torch.from_numpy(w).cuda(), torch.from_numpy(x).cuda(), None, g, ls.FP32, want_tex=False, act_save=act)
+    torch.cuda.synchronize()
+    a = _planes(g, 2, act)
+    up = lambda t: t.repeat(2, 1).repeat(2, 2)
+    src = [x.astype(np.float64), a["A1"], a["P1"], a["A3"], a["P2"], a["A5"], np.concatenate([up(a["A6"]), a["A4"]], -1),
+           a["A7"], np.concatenate([up(a["A8"]), a["A2"]], -1), a["A9"]][layer]
+    got = a[["A1", "A2", "A3", "A4", "A5", "A6", "A7", "A8", "A9", "A10"][layer]]
+    want = _conv(src, wl.astype(np.float64), w[off + co * 9 * ci:off + co * 9 * ci + co].astype(np.float64))
+    assert (want == np.inf).any() or value < 0
+    _same(got, want, 1e-5)
