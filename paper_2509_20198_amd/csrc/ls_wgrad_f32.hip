@@ -17,7 +17,7 @@
 // Bound: at small batches the exposed staging of the one or two tiles a
 // workgroup gets, else the matrix cores (nine products per ten LDS reads, ten
 // where the bias is summed; five per six with 8 input channels).  24
-// tiles of 96 x 96, all eleven layers: 0.32 ms (40 TFLOP/s); 0.75 ms with the
+// tiles of 96 x 96, all eleven layers: 0.31 ms (41 TFLOP/s); 0.75 ms with the
 // vector kernel this replaced, which staged the im2col columns (each input
 // element nine times).  32 output channels per workgroup took 232 registers
 // (two waves per SIMD) and the same time; capped at 168 they spilled (0.48 ms).
